@@ -85,7 +85,7 @@ def _timed_steps(sim, steps, warmup):
 KERNEL_SOURCES = ("step_impl.hpp", "kernels.hpp", "collide.hpp", "lattice.hpp", "common.hpp",
                   "host.hip")
 # the reverse step's kernels (the fused pass) read the forward gather as well
-ADJOINT_SOURCES = KERNEL_SOURCES + ("adjoint.hip", "adjoint.hpp")
+ADJOINT_SOURCES = KERNEL_SOURCES + ("adjoint_impl.hpp", "adjoint.hpp")
 
 
 def kernel_sources_sha(sources=KERNEL_SOURCES):

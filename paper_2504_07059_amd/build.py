@@ -16,7 +16,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "liblbm_mc.so")
-SOURCES = ["host.hip", "step.hip", "step_d2q9.hip", "step_d3q19.hip", "adjoint.hip",
+SOURCES = ["step_d2q9.hip", "step_d3q19.hip", "step_d3q19_n3.hip", "step_d3q19_n4.hip",
+           "adjoint_d3q19.hip", "adjoint_d2q9.hip", "host.hip", "step.hip", "adjoint.hip",
            "observe.hip", "stream_copy.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -124,16 +124,11 @@ __device__ __forceinline__ void species_moments(float P0, const float (&F)[Lat<L
     dlt = sf;
     const float r = fmaf(P0, L::inv_w0, sf);
     rho = r;
-    if (fabsf(r) > kRhoTiny) {
-        const float cr = c * rcp_nr(r);
-        ue[0] = fmaf(jx, cr, 0.5f * g[0]);
-        ue[1] = fmaf(jy, cr, 0.5f * g[1]);
-        ue[2] = fmaf(jz, cr, 0.5f * g[2]);
-    } else {
-        ue[0] = 0.5f * g[0];
-        ue[1] = 0.5f * g[1];
-        ue[2] = 0.5f * g[2];
-    }
+    const bool live = fabsf(r) > kRhoTiny;
+    const float cr = c * rcp_nr(r);
+    ue[0] = live ? fmaf(jx, cr, 0.5f * g[0]) : 0.5f * g[0];
+    ue[1] = live ? fmaf(jy, cr, 0.5f * g[1]) : 0.5f * g[1];
+    ue[2] = live ? fmaf(jz, cr, 0.5f * g[2]) : 0.5f * g[2];
 }
 
 // Store transform: from the deviations gt_a = f~_a - w_a rho (a >= 1) with

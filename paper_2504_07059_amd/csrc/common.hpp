@@ -70,6 +70,7 @@ struct Launch {
     int32_t ntiles;
     int32_t grid;        // work-groups launched (== ntiles when not persistent)
     int32_t bx, by;      // work-group shape (columns)
+    int32_t one;         // the context holds one lattice
     int32_t split;       // 0: one thread per column, all species; 1: one wave per species
     int32_t forcing;     // 0: standard forcing term; 1: plus S_diff; 2: minus S_p plus S_rho
                          // plus S_diff (same for every lattice)

@@ -603,6 +603,7 @@ Launch make_launch(lbm_mc_ctx* c, const float* src, float* dst, hipStream_t s) {
     L.bx = c->tune.bx;
     L.by = c->tune.by;
     L.split = c->tune.split;
+    L.one = c->L == 1 ? 1 : 0;
     L.forcing = c->params[0].forcing;
     L.dens = c->dens;
     L.accel = c->accel;
@@ -676,12 +677,13 @@ lbm_mc_status check_flag(lbm_mc_ctx* c) {
     return LBM_MC_OK;
 }
 
-// Tiles of the reverse step: 64 columns (64 x 1 in 2-D, 32 x 2 in 3-D, one
-// wave per species), layers per tile chosen for about eight tiles per
-// compute unit.
+// Tiles of the reverse step: 64 columns, one wave per species (64 x 1; in 3-D
+// 32 x 2 where rows of 64 would leave more lanes idle), layers per tile chosen
+// for about eight tiles per compute unit.
 lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const auto& q = c->params[0];
-    const int bx = c->DIM == 3 ? 32 : 64, by = c->DIM == 3 ? 2 : 1;
+    const bool half = c->DIM == 3 && round_up(q.nx, 32) < round_up(q.nx, 64);
+    const int bx = half ? 32 : 64, by = half ? 2 : 1;
     const int nm = c->DIM == 2 ? q.ny : q.nz;
     const int nxb = (q.nx + bx - 1) / bx, nyb = c->DIM == 3 ? (q.ny + by - 1) / by : 1;
     const int64_t cols = (int64_t)nxb * nyb;

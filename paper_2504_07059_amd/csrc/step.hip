@@ -7,8 +7,8 @@
 
 namespace lbmmc {
 
-template <int LAT>
-hipError_t launch_step_lat(int ns, const Launch& L);
+template <int LAT, int NS>
+hipError_t launch_step_ns(const Launch& L);
 template <int LAT>
 hipError_t launch_init_lat(int ns, const LatParams* lp, int lat, const LatParams& h,
                            const double* x0, const float* accel, float* f0, float* ft,
@@ -17,8 +17,12 @@ template <int LAT>
 hipError_t launch_moments_lat(int ns, const Launch& L, int direct, float* rho, float* x,
                               float* u, float* ueq, float* us, double* partial, int nq);
 
-extern template hipError_t launch_step_lat<0>(int, const Launch&);
-extern template hipError_t launch_step_lat<1>(int, const Launch&);
+extern template hipError_t launch_step_ns<0, 2>(const Launch&);
+extern template hipError_t launch_step_ns<0, 3>(const Launch&);
+extern template hipError_t launch_step_ns<0, 4>(const Launch&);
+extern template hipError_t launch_step_ns<1, 2>(const Launch&);
+extern template hipError_t launch_step_ns<1, 3>(const Launch&);
+extern template hipError_t launch_step_ns<1, 4>(const Launch&);
 extern template hipError_t launch_init_lat<0>(int, const LatParams*, int, const LatParams&,
                                               const double*, const float*, float*, float*,
                                               unsigned*, hipStream_t);
@@ -29,6 +33,14 @@ extern template hipError_t launch_moments_lat<0>(int, const Launch&, int, float*
                                                  float*, float*, double*, int);
 extern template hipError_t launch_moments_lat<1>(int, const Launch&, int, float*, float*, float*,
                                                  float*, float*, double*, int);
+
+template <int LAT>
+static hipError_t launch_step_lat(int ns, const Launch& L) {
+    if (ns == 2) return launch_step_ns<LAT, 2>(L);
+    if (ns == 3) return launch_step_ns<LAT, 3>(L);
+    if (ns == 4) return launch_step_ns<LAT, 4>(L);
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_step(int lattice, int ns, const Launch& L) {
     if (lattice == 0) return launch_step_lat<0>(ns, L);

@@ -18,21 +18,36 @@ namespace lbmmc {
 // Work-groups are dealt to the eight XCDs round-robin by work-group id.  Map
 // the id to a "virtual" id so that the work-groups on one XCD take a
 // contiguous range of the (spatially ordered) tile list and share its halo
-// rows in their XCD's L2.  Bijective for any grid size.
-__device__ __forceinline__ void tile_range(int ntiles, int& t0, int& t1) {
-    const int G = gridDim.x, b = blockIdx.x;
+// rows in their XCD's L2.  Bijective for any grid size G.
+__device__ __forceinline__ int virtual_block(int G) {
+    const int b = blockIdx.x;
     const int k = b & 7, idx = b >> 3, per = G >> 3, rem = G & 7;
-    const int vb = k * per + (k < rem ? k : rem) + idx;
+    return k * per + (k < rem ? k : rem) + idx;
+}
+
+// The tiles of a work-group of a grid that may be smaller than the tile list.
+__device__ __forceinline__ void tile_range(int ntiles, int& t0, int& t1) {
+    const int G = gridDim.x, vb = virtual_block(G);
     if (G == ntiles) {
-        // one tile per work-group (every non-persistent launch): the 64-bit
-        // divisions below are a long scalar sequence at the start of every
-        // wave, 0.1 us of a 6.2 us step on a small lattice
         t0 = vb;
         t1 = vb + 1;
         return;
     }
     t0 = (int)((int64_t)vb * ntiles / G);
     t1 = (int)((int64_t)(vb + 1) * ntiles / G);
+}
+
+// The lattice of tile t (one: the context holds one lattice).  With one
+// lattice the tile and its lattice's constants are two independent reads; the
+// index read first would put a second memory round trip (0.3 us of a 5.7 us
+// step of a small lattice) before everything else.
+__device__ __forceinline__ int tile_lattice(const Tile* __restrict__ tiles, int t, int one) {
+    int lat = 0;
+    if (!one) {
+        lat = __builtin_amdgcn_readfirstlane(tiles[t].lat);
+        asm volatile("" : "+s"(lat));   // (keeps the read in this branch)
+    }
+    return lat;
 }
 
 // Index of node (x, y, layer m) in the dense node fields of a lattice.
@@ -146,8 +161,9 @@ __global__ void __launch_bounds__(256) k_step(const float* __restrict__ src, flo
 // collides and stores its own species.  A wave holds one species' marching
 // state instead of NS, and keeps its marching-axis partial sums in LDS
 // (2 per direction with a marching component: 12 floats per lane in 2-D, 20
-// in 3-D; see kSplitLdsMarch), so several times more waves fit on a SIMD:
-// five in 2-D, four in 3-D (three with the sums in registers).
+// in 3-D; see kSplitLdsMarch), so several times more waves fit on a SIMD: for
+// states beyond the last-level cache seven in 2-D (65 VGPRs), four in 3-D
+// (124; three with the sums in registers).
 //
 // A work-group may hold W such segments of 64 columns side by side
 // (threadIdx.z = segment; bx * by = 64 W): W consecutive 64-column pieces of
@@ -172,27 +188,12 @@ struct SplitOp {
     const LatParams* P;
     int x, y;
     const float* accel;      // EXT 1: the force field
-    // 2-D: the stores of layer m are issued in the next layer's call, after
-    // that layer's gather has its loads back.  A wave's vector memory counter
-    // retires in issue order, so stores issued just before the next layer's
-    // loads would hold the first wait on those loads until the stores are
-    // acknowledged; issued later, their completion overlaps the exchange
-    // barrier and the collision (bit-identical, about 2 % faster per step).
-    // In 3-D they are stored at once: deferred, the step measured far slower.
-    static constexpr bool kDefer = Lat<LAT>::DIM == 2;
-    float out[Q];            // kDefer: the pending layer's values
-    unsigned out_own;
-    bool pend;
-    __device__ __forceinline__ void flush() {
-        if (pend) {
-#pragma unroll
-            for (int a = 0; a < Q; ++a) stb<POL>(D, a, out_own, out[a]);
-        }
-        pend = false;
-    }
+    // added to the stores' offsets: kSolid on lanes beyond the lattice, whose
+    // stores the range check then drops (no branch around them, so the next
+    // layer's loads, issued before them, are waited for alone)
+    unsigned skip;
     __device__ __forceinline__ void operator()(float P0, float (&F)[Q], int m, unsigned own) {
         constexpr int DIM = Lat<LAT>::DIM;
-        if constexpr (kDefer) flush();
         float g[3];
         node_accel<LAT, EXT == 1>(accel, *P, C.g, dense_node<LAT>(*P, x, y, m), g);
         float rho_s, dlt_s, ue_s[3];
@@ -253,20 +254,12 @@ struct SplitOp {
         }
         const bool ok = collide_species<LAT, FRC>(K, g, rho_s, dlt_s, ue_s, M, V, gd, P0, F) &&
                         isfinite(M.R);
-        if (inside) {
-            if constexpr (kDefer) {
-                out[0] = P0;
+        const Buf Dm = fresh(D);
+        const unsigned at = oadd(own, skip);
+        stb<POL>(Dm, 0, at, P0);
 #pragma unroll
-                for (int a = 1; a < Q; ++a) out[a] = F[a];
-                out_own = own;
-                pend = true;
-            } else {
-                stb<POL>(D, 0, own, P0);
-#pragma unroll
-                for (int a = 1; a < Q; ++a) stb<POL>(D, a, own, F[a]);
-            }
-            bad = bad || !ok;
-        }
+        for (int a = 1; a < Q; ++a) stb<POL>(Dm, a, at, F[a]);
+        bad = bad || (inside && !ok);
     }
 };
 
@@ -281,11 +274,16 @@ constexpr bool kSplitLdsMarch = Lat<LAT>::DIM == 3 || POL != kStoreWT;
 // lanes with W <= 4 and NS x W <= 12 (three waves per SIMD).
 constexpr int kSplitMaxThreads = 768;
 
-template <int LAT, int NS, int FRC, int EXT, int POL>
-__global__ void __launch_bounds__(kSplitMaxThreads) k_step_split(
+// LOOP: a persistent grid, whose work-groups run several tiles each.  The
+// usual launch has a work-group per tile and a kernel without the loop: what
+// the loop needs (64-bit divisions, values held across tiles) is a tenth of
+// the instructions of a one-layer tile.
+template <int LAT, int NS, int FRC, int EXT, int POL, bool WAVE, bool LOOP>
+__global__ void __launch_bounds__(kSplitMaxThreads)
+    __attribute__((amdgpu_waves_per_eu(Lat<LAT>::DIM == 3 ? 4 : 3))) k_step_split(
         const float* __restrict__ src, float* __restrict__ dst,
         const LatParams* __restrict__ lps, const Tile* __restrict__ tiles, int ntiles, int bx,
-        const float* __restrict__ dens, const float* __restrict__ accel,
+        int one, const float* __restrict__ dens, const float* __restrict__ accel,
         unsigned* __restrict__ flag) {
     constexpr int DIM = Lat<LAT>::DIM;
     // [FRC == 2 ? 2 : 1][2][W][NS][64] float4: the exchange buffers (and those
@@ -302,17 +300,15 @@ __global__ void __launch_bounds__(kSplitMaxThreads) k_step_split(
     // exchange buffers
     float* macc = reinterpret_cast<float*>(smem + (FRC == 2 ? 2 : 1) * 2 * xstride) +
                   (seg * NS + s) * 2 * kMarDirs<LAT> * 64 + lane;
-    int t0, t1;
-    tile_range(ntiles, t0, t1);
     bool bad = false;
-    for (int t = t0; t < t1; ++t) {
+    auto run = [&](int t) {
         const Tile T = tiles[t];
-        const LatParams& P = lps[T.lat];
+        const LatParams& P = lps[tile_lattice(tiles, t, one)];
         // lanes beyond the lattice still run (every wave must reach the
         // barriers) and store nothing
-        int x, y;
+        int xs, x, y;
         bool zero;
-        const bool inside = tile_column_seg<LAT>(T, P, lane, bx, seg, W, x, y, zero);
+        const bool inside = tile_column_seg<LAT>(T, P, lane, bx, seg, W, xs, x, y, zero);
         const GatherConst G = gather_const(P, DIM);
         // the species' own constants, read with the uniform species index
         // (scalar loads; no run-time indexing of register arrays)
@@ -325,13 +321,21 @@ __global__ void __launch_bounds__(kSplitMaxThreads) k_step_split(
                                  FRC == 2 ? dens + P.field_base * NS
                                                 + s * ((int64_t)P.nx * P.ny * P.nz)
                                           : nullptr,
-                                 &P, x, y, accel, {}, 0u, false};
-        march1<LAT, decltype(op), kSplitLdsMarch<LAT, POL>>(
-                species_buf<LAT>(src + P.base, P.plane, s), G, s, L, x, y, zero, bx % 64 == 0,
-                T.m0, T.m1, op, macc);
-        op.flush();
+                                 &P, x, y, accel, inside ? 0u : kSolid};
+        march1<LAT, WAVE, kSplitLdsMarch<LAT, POL>, DIM == 2>(
+                species_buf<LAT>(src + P.base, P.plane, s), G, s, L, xs, x, y, zero, T.m0, T.m1,
+                op, macc);
         bad = bad || op.bad;
-        __syncthreads();   // the next tile reuses the exchange buffers
+    };
+    if constexpr (LOOP) {
+        int t0, t1;
+        tile_range(ntiles, t0, t1);
+        for (int t = t0; t < t1; ++t) {
+            run(t);
+            if (t + 1 < t1) __syncthreads();   // the next tile reuses the exchange buffers
+        }
+    } else {
+        run(virtual_block(ntiles));
     }
     if (bad) atomicOr(flag, 1u);
 }
@@ -405,7 +409,7 @@ __global__ void __launch_bounds__(256) k_density(const float* __restrict__ src,
 
 // species-split form: block (64, NS, W), wave (s, seg) streams species s on
 // segment seg of the tile
-template <int LAT, int NS>
+template <int LAT, int NS, bool WAVE>
 __global__ void __launch_bounds__(kSplitMaxThreads) k_density_split(
         const float* __restrict__ src, const LatParams* __restrict__ lps,
         const Tile* __restrict__ tiles, int ntiles, int bx, float* __restrict__ dens) {
@@ -419,15 +423,15 @@ __global__ void __launch_bounds__(kSplitMaxThreads) k_density_split(
     for (int t = t0; t < t1; ++t) {
         const Tile T = tiles[t];
         const LatParams& P = lps[T.lat];
-        int x, y;
+        int xs, x, y;
         bool zero;
-        const bool inside = tile_column_seg<LAT>(T, P, lane, bx, seg, W, x, y, zero);
+        const bool inside = tile_column_seg<LAT>(T, P, lane, bx, seg, W, xs, x, y, zero);
         const GatherConst G = gather_const(P, DIM);
         const int64_t nodes = (int64_t)P.nx * P.ny * P.nz;
         const float L[3] = {P.lam[s][0], P.lam[s][1], P.lam[s][2]};
         DensOp1<LAT> op{dens + P.field_base * NS + s * nodes, &P, x, y, inside};
-        march1<LAT>(species_buf<LAT>(src + P.base, P.plane, s), G, s, L, x, y, zero,
-                    bx % 64 == 0, T.m0, T.m1, op);
+        march1<LAT, WAVE, false, DIM == 2>(species_buf<LAT>(src + P.base, P.plane, s), G, s, L, xs,
+                                           x, y, zero, T.m0, T.m1, op, nullptr);
     }
 }
 
@@ -660,8 +664,8 @@ __global__ void __launch_bounds__(256) k_moments(const float* __restrict__ src,
 // Calls fn(lattice, species count, forcing, extension) with the four as
 // compile-time constants; extension 0: constant g and resting walls, 1: a
 // force field, 2: moving walls, 3: the equilibrium comparison boundary.
-template <int LAT, typename Fn>
-static hipError_t by_shape(int ns, int frc, int ext, Fn&& fn) {
+template <int LAT, int NS, typename Fn>
+static hipError_t by_shape(int frc, int ext, Fn&& fn) {
     using std::integral_constant;
     constexpr integral_constant<int, LAT> lat{};
     auto with_ext = [&](auto n, auto f) -> hipError_t {
@@ -677,16 +681,24 @@ static hipError_t by_shape(int ns, int frc, int ext, Fn&& fn) {
         if (frc == 2) return with_ext(n, integral_constant<int, 2>{});
         return hipErrorInvalidValue;
     };
-    if (ns == 2) return with_frc(integral_constant<int, 2>{});
-    if (ns == 3) return with_frc(integral_constant<int, 3>{});
-    if (ns == 4) return with_frc(integral_constant<int, 4>{});
-    return hipErrorInvalidValue;
+    return with_frc(integral_constant<int, NS>{});
 }
 
-template <int LAT_>
-hipError_t launch_step_lat(int ns, const Launch& L) {
-    if (L.split && !split_shape_ok(L.bx, L.by, ns)) return hipErrorInvalidValue;
-    return by_shape<LAT_>(ns, L.forcing, L.eqb ? 3 : (L.accel ? 1 : (L.moving ? 2 : 0)),
+// Calls go(wave): the wave form where the 64 lanes of a wave are consecutive
+// columns of a row (always in 2-D), else (3-D column blocks narrower than 64)
+// every value by a load of its own.
+template <int LAT, class Go>
+static hipError_t by_wave(int bx, Go go) {
+    if constexpr (Lat<LAT>::DIM == 3) {
+        if (bx % 64) return go(std::false_type{});
+    }
+    return go(std::true_type{});
+}
+
+template <int LAT_, int NS_>
+hipError_t launch_step_ns(const Launch& L) {
+    if (L.split && !split_shape_ok(L.bx, L.by, NS_)) return hipErrorInvalidValue;
+    return by_shape<LAT_, NS_>(L.forcing, L.eqb ? 3 : (L.accel ? 1 : (L.moving ? 2 : 0)),
                     [&](auto lat, auto n, auto frc, auto ex) -> hipError_t {
         constexpr int LAT = decltype(lat)::value, NS = decltype(n)::value,
                       FRC = decltype(frc)::value, EXT = decltype(ex)::value;
@@ -701,10 +713,18 @@ hipError_t launch_step_lat(int ns, const Launch& L) {
                                        (kSplitLdsMarch<LAT, POL>
                                             ? (size_t)W * NS * 2 * kMarDirs<LAT> * 64 * sizeof(float)
                                             : 0);
-                    hipLaunchKernelGGL((k_step_split<LAT, NS, FRC, EXT, POL>), dim3(L.grid),
-                                       dim3(64, NS, W), lds, L.stream, L.src, L.dst, L.lp,
-                                       L.tiles, L.ntiles, L.bx, L.dens, L.accel, L.flag);
-                    return hipGetLastError();
+                    auto go = [&](auto wave, auto loop) {
+                        hipLaunchKernelGGL(
+                            (k_step_split<LAT, NS, FRC, EXT, POL, decltype(wave)::value,
+                                          decltype(loop)::value>),
+                            dim3(L.grid), dim3(64, NS, W), lds, L.stream, L.src, L.dst, L.lp,
+                            L.tiles, L.ntiles, L.bx, L.one, L.dens, L.accel, L.flag);
+                        return hipGetLastError();
+                    };
+                    return by_wave<LAT>(L.bx, [&](auto wave) {
+                        return L.grid == L.ntiles ? go(wave, std::false_type{})
+                                                  : go(wave, std::true_type{});
+                    });
                 }
             }
             hipLaunchKernelGGL((k_step<LAT, NS, FRC, EXT, POL>), dim3(L.grid), dim3(L.bx, L.by),
@@ -725,14 +745,19 @@ hipError_t launch_step_lat(int ns, const Launch& L) {
             if (FRC == 2) {
                 if (!L.dens) return hipErrorInvalidValue;
                 // (the force does not enter the densities)
-                if (L.split)
-                    hipLaunchKernelGGL((k_density_split<LAT, NS>), dim3(L.grid),
-                                       dim3(64, NS, L.bx * L.by / 64), 0, L.stream, L.src, L.lp,
-                                       L.tiles, L.ntiles, L.bx, L.dens);
-                else
+                hipError_t e;
+                if (L.split) {
+                    e = by_wave<LAT>(L.bx, [&](auto wave) {
+                        hipLaunchKernelGGL((k_density_split<LAT, NS, decltype(wave)::value>),
+                                           dim3(L.grid), dim3(64, NS, L.bx * L.by / 64), 0,
+                                           L.stream, L.src, L.lp, L.tiles, L.ntiles, L.bx, L.dens);
+                        return hipGetLastError();
+                    });
+                } else {
                     hipLaunchKernelGGL((k_density<LAT, NS>), dim3(L.grid), dim3(L.bx, L.by), 0,
                                        L.stream, L.src, L.lp, L.tiles, L.ntiles, L.dens);
-                const hipError_t e = hipGetLastError();
+                    e = hipGetLastError();
+                }
                 if (e != hipSuccess) return e;
             }
             return L.wt ? step(std::integral_constant<int, kStoreWT>{})
@@ -741,14 +766,14 @@ hipError_t launch_step_lat(int ns, const Launch& L) {
     });
 }
 
-template <int LAT_>
-hipError_t launch_init_lat(int ns, const LatParams* lp, int lat, const LatParams& h,
-                           const double* x0, const float* accel, float* f0, float* ft,
-                           unsigned* flag, hipStream_t s) {
+template <int LAT_, int NS_>
+static hipError_t launch_init_ns(const LatParams* lp, int lat, const LatParams& h,
+                                 const double* x0, const float* accel, float* f0, float* ft,
+                                 unsigned* flag, hipStream_t s) {
     const int64_t nodes = (int64_t)h.nx * h.ny * h.nz;
     const int64_t blocks = std::min<int64_t>((nodes + 255) / 256, 65536);
     // the initial collision acts on f(0), which has not been streamed: no wall terms
-    return by_shape<LAT_>(ns, h.forcing, accel ? 1 : 0,
+    return by_shape<LAT_, NS_>(h.forcing, accel ? 1 : 0,
                     [&](auto la, auto n, auto frc, auto ex) {
         constexpr int LAT = decltype(la)::value, NS = decltype(n)::value,
                       FRC = decltype(frc)::value, EXT = decltype(ex)::value;
@@ -760,6 +785,16 @@ hipError_t launch_init_lat(int ns, const LatParams* lp, int lat, const LatParams
             return hipGetLastError();
         }
     });
+}
+
+template <int LAT>
+hipError_t launch_init_lat(int ns, const LatParams* lp, int lat, const LatParams& h,
+                           const double* x0, const float* accel, float* f0, float* ft,
+                           unsigned* flag, hipStream_t s) {
+    if (ns == 2) return launch_init_ns<LAT, 2>(lp, lat, h, x0, accel, f0, ft, flag, s);
+    if (ns == 3) return launch_init_ns<LAT, 3>(lp, lat, h, x0, accel, f0, ft, flag, s);
+    if (ns == 4) return launch_init_ns<LAT, 4>(lp, lat, h, x0, accel, f0, ft, flag, s);
+    return hipErrorInvalidValue;
 }
 
 template <int LAT, int NS>
