@@ -554,23 +554,9 @@ lbm_mc_status build_tiles(lbm_mc_ctx* c) {
     return LBM_MC_OK;
 }
 
-// Default execution shape: 64-column tiles, one wave per species, with as
-// many layers per tile as keep about eight tiles per compute unit (long
-// marches reuse the three-layer register stencil; short ones fill the chip on
-// small lattices).
-Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int cus) {
-    auto columns = [&](int bx, int by) {
-        int64_t n = 0;
-        for (int l = 0; l < n_lattices; ++l)
-            n += (int64_t)((p[l].nx + bx - 1) / bx) *
-                 (dim == 3 ? (p[l].ny + by - 1) / by : 1);
-        return n;
-    };
-    auto layers = [&]() {
-        int64_t m = 0;
-        for (int l = 0; l < n_lattices; ++l) m = std::max<int64_t>(m, dim == 3 ? p[l].nz : p[l].ny);
-        return m;
-    };
+// Default execution shape: 64-column tiles, one wave per species, with the
+// layers per tile that fill the chip in the fewest layer rounds.
+Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, int cus) {
     // the species-split variant over 64-column rows: as fast as or faster
     // than one thread per column on every workload measured (it keeps several
     // times more waves per SIMD)
@@ -578,9 +564,31 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int cus) 
     t.bx = 64;
     t.by = 1;
     t.split = 1;
-    const int64_t cols = columns(t.bx, t.by);
-    int64_t rows = cols * layers() / (8 * (int64_t)cus);
-    t.rows = (int)std::max<int64_t>(1, std::min<int64_t>(dim == 3 ? 16 : 32, rows));
+    // Layers per tile: a tile of r layers gathers r + 1 (the halo of its first
+    // and last), and the chip holds `cap` of these work-groups at a time (one
+    // wave per species, 6 waves per SIMD in 2-D and 4 in 3-D), so a launch
+    // takes about ceil(tiles / cap) rounds of r + 1 layers; the shortest tile
+    // of the least total is taken.  us per step at r = 1, 2, 4, 6, 8, 16, 32:
+    // 4096x1024 three species 231, 199, 190, 189, 190, 196, 204 (6 taken);
+    // 512x512 binary 9.8, 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary
+    // 40, 37.2, 37.9, 42, 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).
+    // Against eight tiles per compute unit, up to 32 layers (16 in 3-D), taken
+    // before: 4096x1024 204 -> 189, 3001x700 with all forcing terms 178 -> 151,
+    // 512 tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
+    const int64_t cap = (int64_t)cus * (4 * (dim == 3 ? 4 : 6) / ns);
+    int64_t least = INT64_MAX;
+    for (int r = 1; r <= (dim == 3 ? 16 : 6); ++r) {
+        int64_t tiles = 0;
+        for (int l = 0; l < n_lattices; ++l) {
+            const int64_t cols = (int64_t)((p[l].nx + 63) / 64) * (dim == 3 ? p[l].ny : 1);
+            tiles += cols * (((dim == 3 ? p[l].nz : p[l].ny) + r - 1) / r);
+        }
+        const int64_t cost = (tiles + cap - 1) / cap * (r + 1);
+        if (cost < least) {
+            least = cost;
+            t.rows = r;
+        }
+    }
     t.persistent = 0;
     return t;
 }
@@ -965,7 +973,7 @@ static lbm_mc_status init_impl(const lbm_mc_params* p, int32_t n_lattices, const
         return bail(fail(LBM_MC_ERR_HIP, "memset failed"));
 
     // default execution shape, or a cached autotuned one
-    Tuning t = default_tuning(p, n_lattices, c->DIM, c->cus);
+    Tuning t = default_tuning(p, n_lattices, c->DIM, c->N, c->cus);
     if (lattice_has_eq(p[0])) {
         t.split = 0;   // the equilibrium boundary runs one thread per column
     } else {
