@@ -12,8 +12,8 @@
 //
 // Reduction: work-group (bx, c) owns 64 columns and the c-th chunk of rows; it
 // writes one FP64 partial sum per (chunk, species, column) into a scratch
-// array, and a second kernel adds the chunks of each (species, column) in
-// chunk order.  The result does not depend on timing (no atomics).
+// array, and a second kernel adds the chunks of each (species, column) in a
+// fixed order.  The result does not depend on timing (no atomics).
 #include <hip/hip_runtime.h>
 
 #include <map>
@@ -86,16 +86,30 @@ __global__ void __launch_bounds__(64) k_profile_part(const float* __restrict__ s
     for (int i = 0; i < NS; ++i) part[((int64_t)c * NS + i) * P.nx + x] = acc[i];
 }
 
-// xbar[i * nx + x] = (sum over chunks in order) / rows
-__global__ void __launch_bounds__(256) k_profile_sum(const LatParams* __restrict__ lps, int ns,
-                                                     int nchunks, const double* __restrict__ part,
-                                                     double* __restrict__ xbar) {
+// xbar[i * nx + x] = (sum over chunks) / rows: wave w of the 16 adds chunks w,
+// w + 16, ... of 64 sums, then the waves' parts are added in wave order.  Bound
+// by the latency of the chain of loads: with one thread per sum and up to 2048
+// chunks it took 258 us for the profile of a 128x96x64 box (512 sums, 1024
+// chunks), as long as the reads of the state; now 11 us.
+__global__ void __launch_bounds__(1024) k_profile_sum(const LatParams* __restrict__ lps, int ns,
+                                                      int nchunks, const double* __restrict__ part,
+                                                      double* __restrict__ xbar) {
+    __shared__ double red[16][64];
     const LatParams& P = lps[0];
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = (int)threadIdx.x, w = (int)threadIdx.y;
     const int64_t total = (int64_t)ns * P.nx;
-    if (k >= total) return;
+    const int64_t k = (int64_t)blockIdx.x * 64 + lane;
     double v = 0.0;
-    for (int c = 0; c < nchunks; ++c) v += part[(int64_t)c * total + k];
+    if (k < total) {
+#pragma unroll 8
+        for (int c = w; c < nchunks; c += 16) v += part[(int64_t)c * total + k];
+    }
+    red[w][lane] = v;
+    __syncthreads();
+    if (w != 0 || k >= total) return;
+    v = 0.0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v += red[j][lane];
     xbar[k] = v / ((double)P.ny * (double)P.nz);
 }
 
@@ -164,7 +178,7 @@ hipError_t launch_profile(int lattice, int ns, const LatParams* lp, const LatPar
     });
     if (e != hipSuccess) return e;
     const int64_t total = (int64_t)ns * h.nx;
-    hipLaunchKernelGGL(k_profile_sum, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, lp,
+    hipLaunchKernelGGL(k_profile_sum, dim3((unsigned)((total + 63) / 64)), dim3(64, 16), 0, st, lp,
                        ns, nchunks, part, xbar);
     return hipGetLastError();
 }

@@ -64,30 +64,38 @@ hipError_t launch_moments(int lattice, int ns, const Launch& L, int direct, floa
 }
 
 // Fixed-order FP64 sum of the per-tile partials of each lattice: one
-// work-group per lattice, thread t takes tiles begin+t, begin+t+256, ..., then
-// a fixed shuffle and LDS tree (reproducible run to run).
-__global__ void __launch_bounds__(256) k_reduce(const LatParams* __restrict__ lps, int nlat,
+// work-group per lattice and quantity, thread t takes tiles begin+t,
+// begin+t+256, ..., then a fixed shuffle and LDS tree (reproducible run to
+// run).  Bound by the latency of its loads, so eight are in flight at a time:
+// 66 us for the 16384 tiles and six quantities of the 4096x1024 tube one load
+// after the other in one work-group, 18 us now.
+__global__ void __launch_bounds__(256) k_reduce(const LatParams* __restrict__ lps,
                                                 const double* __restrict__ partial, int nq,
                                                 double* __restrict__ totals) {
     __shared__ double red[4];
-    const int l = blockIdx.x;
+    const int l = blockIdx.x, q = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = lps[l].tile_begin, t1 = lps[l].tile_end;
-    for (int q = 0; q < nq; ++q) {
-        double v = 0.0;
-        for (int t = t0 + tid; t < t1; t += 256) v += partial[(int64_t)t * nq + q];
+    double v = 0.0;
+    int t = t0 + tid;
+    for (; t + 7 * 256 < t1; t += 8 * 256) {
+        double r[8];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) red[wave] = v;
-        __syncthreads();
-        if (tid == 0) totals[(int64_t)l * nq + q] = (red[0] + red[1]) + (red[2] + red[3]);
-        __syncthreads();
+        for (int k = 0; k < 8; ++k) r[k] = partial[(int64_t)(t + k * 256) * nq + q];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v += r[k];
     }
+    for (; t < t1; t += 256) v += partial[(int64_t)t * nq + q];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) red[wave] = v;
+    __syncthreads();
+    if (tid == 0) totals[(int64_t)l * nq + q] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 hipError_t launch_reduce(const LatParams* lp, int nlat, const double* partial, int nq,
                          double* totals, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce, dim3(nlat), dim3(256), 0, s, lp, nlat, partial, nq, totals);
+    hipLaunchKernelGGL(k_reduce, dim3(nlat, nq), dim3(256), 0, s, lp, partial, nq, totals);
     return hipGetLastError();
 }
 

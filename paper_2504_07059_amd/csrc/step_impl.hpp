@@ -660,6 +660,161 @@ __global__ void __launch_bounds__(256) k_moments(const float* __restrict__ src,
     }
 }
 
+// Species-split form: block (64, NS, W) as in the step.  Wave (s, seg) streams
+// species s on segment seg of the tile, hands its density and velocity to the
+// other species' waves through LDS, and writes its own species' fields and
+// sums; the barycentric velocity's component d is wave d's (component 2 wave
+// 0's where there are two species).  Bound by the loads, like the density
+// pass: with one thread per column the node's 27 rows stood in one wave's
+// registers, 305 us for the density and velocity of the three-species
+// 4096x1024 tube (0.45 GB read) in tiles of 32 rows and about 230 in tiles of 4;
+// this form 178 us in those.
+template <int LAT, int NS>
+struct MomOp1 {
+    static constexpr int Q = Lat<LAT>::Q;
+    static constexpr int DIM = Lat<LAT>::DIM;
+    float* rho_out;          // the lattice's fields, as in MomOp
+    float* x_out;
+    float* u_out;
+    float* ueq_out;
+    float* us_out;
+    int64_t nodes;
+    int x, y, s, lane;
+    bool inside;
+    CollConst C;
+    float c;                 // this species' lattice speed
+    const float* accel;      // this lattice's force field, or null (constant g)
+    const LatParams* P;
+    float4* xch;             // [2][W][NS][64] exchange buffers in LDS
+    int xstride;
+    double mass, mom[2];     // sums of this wave's rho_s and U components
+    __device__ __forceinline__ void operator()(float P0, float (&F)[Q], int m, unsigned) {
+        const int64_t node = dense_node<LAT>(*P, x, y, m);
+        float g[3] = {C.g[0], C.g[1], C.g[2]};
+        if (accel) {
+            g[0] = accel[node];
+            g[1] = accel[nodes + node];
+            g[2] = DIM == 3 ? accel[2 * nodes + node] : 0.0f;
+        }
+        float rho_s, dlt_s, ue_s[3];
+        species_moments<LAT>(P0, F, c, g, rho_s, dlt_s, ue_s);
+        float4* X = xch + (m & 1) * xstride;
+        X[s * 64 + lane] = make_float4(rho_s, ue_s[0], ue_s[1], ue_s[2]);
+        __syncthreads();
+        float rho[NS], ue[NS][3];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const float4 v = X[j * 64 + lane];
+            rho[j] = v.x;
+            ue[j][0] = v.y;
+            ue[j][1] = v.z;
+            ue[j][2] = v.w;
+        }
+        WallMove W;
+        if (moving_wall_at(*P, x, DIM == 2 ? m : y, DIM == 2 ? 0 : m, W))
+            wall_shift_ue<NS>(W, rho, ue);
+        float R = 0.0f, n = 0.0f, U[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            R += rho[j];
+            n += rho[j] * C.invM[j];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) U[d] = fmaf(rho[j], ue[j][d], U[d]);
+        }
+        const float iR = 1.0f / R;
+        if (!inside) return;
+        mass += (double)rho_s;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            if (j != s) continue;   // (s is uniform over the wave)
+            if (rho_out) rho_out[j * nodes + node] = rho[j];
+            if (x_out) x_out[j * nodes + node] = rho[j] * C.invM[j] / n;
+            if (ueq_out) {
+#pragma unroll
+                for (int d = 0; d < DIM; ++d) ueq_out[(j * DIM + d) * nodes + node] = ue[j][d];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            if (d % NS != s) continue;
+            if (u_out) u_out[d * nodes + node] = U[d] * iR;
+            mom[d / NS] += (double)U[d];
+        }
+        if (us_out) {
+            const Mix Mx = mixture<NS>(rho, ue, C);
+            float y[NS][NS];
+            tau_solve<NS>(rho, Mx.R, Mx.n, C, y);
+#pragma unroll
+            for (int j = 0; j < NS; ++j) {
+                if (j != s) continue;
+                float V[3];
+                friction<NS>(j, rho, ue, y, Mx.iR, V);
+#pragma unroll
+                for (int d = 0; d < DIM; ++d)
+                    us_out[(j * DIM + d) * nodes + node] = fmaf(-0.5f, V[d], ue[j][d]);
+            }
+        }
+    }
+};
+
+template <int LAT, int NS, bool WAVE>
+__global__ void __launch_bounds__(kSplitMaxThreads) k_moments_split(
+        const float* __restrict__ src, const LatParams* __restrict__ lps,
+        const Tile* __restrict__ tiles, int ntiles, int bx, const float* __restrict__ accel,
+        float* rho, float* xo, float* u, float* ueq, float* us, double* __restrict__ partial,
+        int nq) {
+    constexpr int DIM = Lat<LAT>::DIM;
+    extern __shared__ float4 smem[];   // [2][W][NS][64]
+    __shared__ double red[4][NS + 3];
+    const int lane = (int)threadIdx.x;
+    const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const int seg = __builtin_amdgcn_readfirstlane((int)threadIdx.z);
+    const int W = (int)blockDim.z;
+    const int t = virtual_block(ntiles);
+    const Tile T = tiles[t];
+    const LatParams& P = lps[T.lat];
+    int xs, x, y;
+    bool zero;
+    const bool inside = tile_column_seg<LAT>(T, P, lane, bx, seg, W, xs, x, y, zero);
+    const GatherConst G = gather_const(P, DIM);
+    const float L[3] = {P.lam[s][0], P.lam[s][1], P.lam[s][2]};
+    MomOp1<LAT, NS> op;
+    op.rho_out = rho ? rho + P.field_base * NS : nullptr;
+    op.x_out = xo ? xo + P.field_base * NS : nullptr;
+    op.u_out = u ? u + P.field_base * DIM : nullptr;
+    op.ueq_out = ueq ? ueq + P.field_base * NS * DIM : nullptr;
+    op.us_out = us ? us + P.field_base * NS * DIM : nullptr;
+    op.nodes = (int64_t)P.nx * P.ny * P.nz;
+    op.x = x; op.y = y; op.s = s; op.lane = lane;
+    op.inside = inside;
+    op.C = coll_const(P);
+    op.c = P.c[s];
+    op.accel = accel ? accel + P.field_base * DIM : nullptr;
+    op.P = &P;
+    op.xch = smem + seg * NS * 64;
+    op.xstride = W * NS * 64;
+    op.mass = op.mom[0] = op.mom[1] = 0.0;
+    march1<LAT, WAVE, false, DIM == 2>(species_buf<LAT>(src + P.base, P.plane, s), G, s, L, xs, x,
+                                       y, zero, T.m0, T.m1, op, nullptr);
+    // block reduction: wave shuffles, then the segments in a fixed order
+    auto put = [&](int q, double v) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) red[seg][q] = v;
+    };
+    put(s, op.mass);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d)
+        if (d % NS == s) put(NS + d, op.mom[d / NS]);
+    __syncthreads();
+    const int tid = lane + 64 * (s + NS * seg);
+    if (tid < NS + DIM) {
+        double v = 0.0;
+        for (int w = 0; w < W; ++w) v += red[w][tid];
+        partial[(int64_t)t * nq + tid] = v;
+    }
+}
+
 // ---------------------------------------------------------------- launchers
 // Calls fn(lattice, species count, forcing, extension) with the four as
 // compile-time constants; extension 0: constant g and resting walls, 1: a
@@ -800,6 +955,18 @@ hipError_t launch_init_lat(int ns, const LatParams* lp, int lat, const LatParams
 template <int LAT, int NS>
 static hipError_t launch_moments_t(const Launch& L, int direct, float* rho, float* x, float* u,
                                    float* ueq, float* us, double* partial, int nq) {
+    // (the initial state f(0) is read in place, one thread per column)
+    if (L.split && !direct) {
+        if (!split_shape_ok(L.bx, L.by, NS)) return hipErrorInvalidValue;
+        const int W = L.bx * L.by / 64;
+        return by_wave<LAT>(L.bx, [&](auto wave) {
+            hipLaunchKernelGGL((k_moments_split<LAT, NS, decltype(wave)::value>),
+                               dim3(L.ntiles), dim3(64, NS, W),
+                               2 * (size_t)W * NS * 64 * sizeof(float4), L.stream, L.src, L.lp,
+                               L.tiles, L.ntiles, L.bx, L.accel, rho, x, u, ueq, us, partial, nq);
+            return hipGetLastError();
+        });
+    }
     if (L.eqb)
         hipLaunchKernelGGL((k_moments<LAT, NS, true>), dim3(L.ntiles), dim3(L.bx, L.by), 0,
                            L.stream, L.src, L.lp, L.tiles, direct, L.accel, rho, x, u, ueq, us,
