@@ -75,21 +75,42 @@ struct AdjSplitOp {
     bool inside;
     // Build of the fused pass for three waves per SIMD: 2-D, up to three
     // species, states beyond the last-level cache (non-temporal stores).
-    // Its marching and gradient sums then live in LDS and its stores are not
-    // deferred; on cache-resident lattices, where one tile's chain sets the
-    // step time, the register build is faster.
+    // Its marching and gradient sums then live in LDS; on cache-resident
+    // lattices, where one tile's chain sets the step time, the register build
+    // is faster.
     static constexpr bool kThree = Lat<LAT>::DIM == 2 && NS <= 3 && POL == kStoreNT;
-    // FP64 gradient sums of this lane: in registers, or in LDS (accl: this
-    // lane's element of the wave's [NG][64] doubles) in 3-D, which keeps the
-    // D3Q19 kernels at two waves per SIMD with four species, and for kThree
+    // FP64 gradient sums of this lane, in registers, or in 3-D and for kThree
+    // in LDS.  Every wave holds the same dL/dK: the species-0 wave alone adds
+    // it (acck: this lane's element of the work-group's [pairs][64] doubles);
+    // dL/dg is each species' own (accl: of the wave's [3][64] doubles).
+    // (Three species in 3-D with dL/dg in registers: a fourth work-group per
+    // compute unit, but 30 registers spilled; 187 against 166 us per reverse
+    // step of 128x96x64.)
+    static constexpr int NP = NS * (NS - 1) / 2;
     static constexpr bool kLdsSums = Lat<LAT>::DIM == 3 || kThree;
-    double accr[kLdsSums ? 1 : NG];
+    double accr[kLdsSums ? 1 : 3];
+    double acckr[kLdsSums ? 1 : NP];
     double* accl;
-    __device__ __forceinline__ double& acc(int q) {
+    double* acck;
+    __device__ __forceinline__ double& accg(int d) {
         if constexpr (kLdsSums)
-            return accl[q * 64];
+            return accl[d * 64];
         else
-            return accr[q];
+            return accr[d];
+    }
+    __device__ __forceinline__ double& accp(int k) {
+        if constexpr (kLdsSums)
+            return acck[k * 64];
+        else
+            return acckr[k];
+    }
+    __device__ __forceinline__ void clear_sums() {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) accg(d) = 0.0;
+        if (s == 0) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) accp(k) = 0.0;
+        }
     }
     // 2-D, up to three species: the loads of a layer are issued before the
     // collision VJP of the layer before it, whose two exchanges hide their
@@ -206,20 +227,27 @@ struct AdjSplitOp {
 #pragma unroll
         for (int a = 0; a < Q; ++a) stb<POL>(Mm, a, at, lt[a]);
         if (inside) {
-            int k = 0;
-            // every wave holds the same dL/dK: the species-0 wave adds it
+            if (s == 0) {
+                int k = 0;
 #pragma unroll
-            for (int i = 0; i < NS; ++i)
+                for (int i = 0; i < NS; ++i)
 #pragma unroll
-                for (int j = i + 1; j < NS; ++j, ++k) acc(k) += s == 0 ? (double)dK[i][j] : 0.0;
+                    for (int j = i + 1; j < NS; ++j, ++k) accp(k) += (double)dK[i][j];
+            }
 #pragma unroll
-            for (int d = 0; d < 3; ++d) acc(k + d) += (double)dg[d];
+            for (int d = 0; d < 3; ++d) accg(d) += (double)dg[d];
         }
     }
     // the wave's sums, for the block reduction
     __device__ __forceinline__ void sums(double (&out)[NG]) {
 #pragma unroll
-        for (int q = 0; q < NG; ++q) out[q] = acc(q);
+        for (int k = 0; k < NP; ++k) out[k] = 0.0;
+        if (s == 0) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) out[k] = accp(k);
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) out[NP + d] = accg(d);
     }
 };
 
@@ -234,21 +262,23 @@ __global__ void __launch_bounds__(256) k_adj_collide(const float* __restrict__ f
     using Op = AdjSplitOp<LAT, NS, POL>;
     __shared__ float x1[NS][4][64];
     __shared__ float x2[NS][Op::KX][64];
-    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::NG][64];
+    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? 3 : 1][64];
+    __shared__ double ksum[Op::kLdsSums ? Op::NP : 1][64];
     // 3-D: the march's partial sums of every wave
     __shared__ float msum[Lat<LAT>::DIM == 3 ? NS - 1 : 1][2 * kMarDirs<LAT>][64];
     const int lane = (int)threadIdx.x;
     const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
-    const Tile T = tiles[blockIdx.x];
+    const int tb = virtual_block((int)gridDim.x);
+    const Tile T = tiles[tb];
     const LatParams& P = lps[0];   // (single-lattice contexts)
     int x, y;
     bool zero;
     const bool inside = tile_column<LAT>(T, P, lane, bx, x, y, zero);
     Op op{species_buf<LAT>(lam + P.base, P.plane, s), species_buf<LAT>(mu + P.base, P.plane, s),
-          coll_const(P), x1, x2, s, lane, inside, {}, &gsum[Op::kLdsSums ? s : 0][0][lane],
+          coll_const(P), x1, x2, s, lane, inside, {}, {}, &gsum[Op::kLdsSums ? s : 0][0][lane],
+          &ksum[0][lane],
           inside ? 0u : kSolid};
-#pragma unroll
-    for (int q = 0; q < Op::NG; ++q) op.acc(q) = 0.0;
+    op.clear_sums();
     const GatherConst G = gather_const(P, DIM);
     const float L[3] = {P.lam[s][0], P.lam[s][1], P.lam[s][2]};
     march1<LAT, WAVE, DIM == 3, Op::kAhead>(species_buf<LAT>(fprev + P.base, P.plane, s), G, s, L,
@@ -256,7 +286,7 @@ __global__ void __launch_bounds__(256) k_adj_collide(const float* __restrict__ f
                                             &msum[DIM == 3 && s > 0 ? s - 1 : 0][0][lane]);
     double sums[Op::NG];
     op.sums(sums);
-    block_reduce_add<Op::NG>(sums, gpart + (int64_t)blockIdx.x * Op::NG);
+    block_reduce_add<Op::NG>(sums, gpart + (int64_t)tb * Op::NG);
 }
 
 // ------------------------------------------------------------------ kernel B
@@ -606,8 +636,8 @@ __device__ __forceinline__ void rev_march_wave(const Buf& M, const GatherConst& 
 // gather of f(t) from f~(t-1) (B: the species' view of the state) and the
 // reversed gather of the later step's mu (M), then op(P0, F, lam_f, own).
 // Both marches' partial sums in LDS in 3-D (20 floats per lane each; species
-// 0, the exact shift, has none), which keeps the fused pass at two waves per
-// SIMD for up to four species, and for Op::kThree.
+// 0, the exact shift, has none), which keeps the fused pass at three waves per
+// SIMD (two with four species), and for Op::kThree.
 template <int LAT, class Op>
 __device__ __forceinline__ void march_fused(const Buf& B, const Buf& M, const GatherConst& G,
                                             int s, const float (&L)[3], const ColGeom& g, int m0,
@@ -690,7 +720,8 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
     constexpr int DIM = Lat<LAT>::DIM;
     const int lane = (int)threadIdx.x;
     const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
-    const Tile T = tiles[blockIdx.x];
+    const int tb = virtual_block((int)gridDim.x);
+    const Tile T = tiles[tb];
     const LatParams& P = lps[0];   // (single-lattice contexts)
     // lanes beyond the lattice run along (their neighbours across lanes are
     // the row's last columns) and store nothing
@@ -729,15 +760,18 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
 // would read lam_s(t); the adjoint stays in population space between the two,
 // so the storage transform and its inverse drop out, and mu(t) goes to mu_out.
 // The parameter gradients accumulate as in kernel A.
+// Its two gathers and the collision VJP keep the vector units busy two thirds of
+// the time in 2-D; in 3-D latency bounds it, at few waves.  Asked for three
+// waves per SIMD the D3Q19 build takes 168 VGPRs (192 with three species before)
+// and a compute unit holds three work-groups instead of two: 128x96x64 with
+// three species 235 -> 167 us per reverse step, tiles and their order included.
 template <int LAT, int NS, int POL, bool WAVE>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(AdjSplitOp<LAT, NS, POL>::kThree ? 3 : 1)))
-    k_adj_fused(const float* __restrict__ fprev,
-                                                   const float* __restrict__ mu_in,
-                                                   float* __restrict__ mu_out,
-                                                   const LatParams* __restrict__ lps,
-                                                   const Tile* __restrict__ tiles, int bx,
-                                                   double* __restrict__ gpart) {
+    __attribute__((amdgpu_waves_per_eu(
+        AdjSplitOp<LAT, NS, POL>::kThree || Lat<LAT>::DIM == 3 ? 3 : 1)))
+    k_adj_fused(const float* __restrict__ fprev, const float* __restrict__ mu_in,
+                float* __restrict__ mu_out, const LatParams* __restrict__ lps,
+                const Tile* __restrict__ tiles, int bx, double* __restrict__ gpart) {
     constexpr int DIM = Lat<LAT>::DIM;
     using Op = AdjSplitOp<LAT, NS, POL>;
     __shared__ float x1[NS][4][64];
@@ -746,12 +780,14 @@ __global__ void __launch_bounds__(256)
     // build)
     constexpr bool HL = Lat<LAT>::DIM == 3 || Op::kThree;
     __shared__ float msum[HL ? NS - 1 : 1][HL ? 4 * kMarDirs<LAT> : 1][64];
-    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::NG][64];
+    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? 3 : 1][64];
+    __shared__ double ksum[Op::kLdsSums ? Op::NP : 1][64];
     const int lane = (int)threadIdx.x;
     const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
     // (species 0, the exact shift, keeps no marching state)
     float* macc = &msum[HL && s > 0 ? s - 1 : 0][0][lane];
-    const Tile T = tiles[blockIdx.x];
+    const int tb = virtual_block((int)gridDim.x);
+    const Tile T = tiles[tb];
     const LatParams& P = lps[0];   // (single-lattice contexts)
     int x, y;
     bool zero;
@@ -759,9 +795,9 @@ __global__ void __launch_bounds__(256)
     const Buf M = species_buf<LAT>(mu_in + P.base, P.plane, s);
     // (the op's stored-adjoint view is not read on this path)
     Op op{M, species_buf<LAT>(mu_out + P.base, P.plane, s), coll_const(P), x1, x2, s, lane,
-          inside, {}, &gsum[Op::kLdsSums ? s : 0][0][lane], inside ? 0u : kSolid};
-#pragma unroll
-    for (int q = 0; q < Op::NG; ++q) op.acc(q) = 0.0;
+          inside, {}, {}, &gsum[Op::kLdsSums ? s : 0][0][lane],
+          &ksum[0][lane], inside ? 0u : kSolid};
+    op.clear_sums();
     const GatherConst G = gather_const(P, DIM);
     const float L[3] = {P.lam[s][0], P.lam[s][1], P.lam[s][2]};
     const Buf B = species_buf<LAT>(fprev + P.base, P.plane, s);
@@ -775,7 +811,7 @@ __global__ void __launch_bounds__(256)
     }
     double sums[Op::NG];
     op.sums(sums);
-    block_reduce_add<Op::NG>(sums, gpart + (int64_t)blockIdx.x * Op::NG);
+    block_reduce_add<Op::NG>(sums, gpart + (int64_t)tb * Op::NG);
 }
 
 // ----------------------------------------------------------------- init VJP

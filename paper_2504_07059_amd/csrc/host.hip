@@ -711,6 +711,24 @@ lbm_mc_status build_tiles(lbm_mc_ctx* c) {
     return LBM_MC_OK;
 }
 
+// Layers per tile of least cost: a tile of r layers gathers r + 1 (the halo of
+// its first and last), and the chip holds `cap` work-groups at a time, so a
+// launch of tiles(r) work-groups takes about ceil(tiles(r) / cap) rounds of
+// r + 1 layers.  The shortest of the cheapest.
+template <class Tiles>
+int cheapest_rows(int max_rows, int64_t cap, Tiles&& tiles) {
+    int best = 1;
+    int64_t least = INT64_MAX;
+    for (int r = 1; r <= max_rows; ++r) {
+        const int64_t cost = (tiles(r) + cap - 1) / cap * (r + 1);
+        if (cost < least) {
+            least = cost;
+            best = r;
+        }
+    }
+    return best;
+}
+
 // Default execution shape: 64-column tiles, one wave per species, with the
 // layers per tile that fill the chip in the fewest layer rounds.
 Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, int cus) {
@@ -721,31 +739,23 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, i
     t.bx = 64;
     t.by = 1;
     t.split = 1;
-    // Layers per tile: a tile of r layers gathers r + 1 (the halo of its first
-    // and last), and the chip holds `cap` of these work-groups at a time (one
-    // wave per species, 6 waves per SIMD in 2-D and 4 in 3-D), so a launch
-    // takes about ceil(tiles / cap) rounds of r + 1 layers; the shortest tile
-    // of the least total is taken.  us per step at r = 1, 2, 4, 6, 8, 16, 32:
-    // 4096x1024 three species 231, 199, 190, 189, 190, 196, 204 (4 taken);
-    // 512x512 binary 9.8, 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary
-    // 40, 37.2, 37.9, 42, 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).
-    // Against eight tiles per compute unit, up to 32 layers (16 in 3-D), taken
-    // before: 4096x1024 204 -> 189, 3001x700 with all forcing terms 178 -> 151,
-    // 512 tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
+    // The chip holds one wave per species, 6 waves per SIMD in 2-D and 4 in
+    // 3-D.  us per step at 1, 2, 4, 6, 8, 16, 32 layers: 4096x1024 three
+    // species 231, 199, 190, 189, 190, 196, 204 (4 taken); 512x512 binary 9.8,
+    // 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary 40, 37.2, 37.9, 42,
+    // 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).  Against eight
+    // tiles per compute unit, up to 32 layers (16 in 3-D), taken before:
+    // 4096x1024 204 -> 189, 3001x700 with all forcing terms 178 -> 151, 512
+    // tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
     const int64_t cap = (int64_t)cus * (4 * (dim == 3 ? 4 : 6) / ns);
-    int64_t least = INT64_MAX;
-    for (int r = 1; r <= (dim == 3 ? 16 : 6); ++r) {
+    t.rows = cheapest_rows(dim == 3 ? 16 : 6, cap, [&](int r) {
         int64_t tiles = 0;
         for (int l = 0; l < n_lattices; ++l) {
             const int64_t cols = (int64_t)((p[l].nx + 63) / 64) * (dim == 3 ? p[l].ny : 1);
             tiles += cols * (((dim == 3 ? p[l].nz : p[l].ny) + r - 1) / r);
         }
-        const int64_t cost = (tiles + cap - 1) / cap * (r + 1);
-        if (cost < least) {
-            least = cost;
-            t.rows = r;
-        }
-    }
+        return tiles;
+    });
     t.persistent = 0;
     return t;
 }
@@ -755,6 +765,19 @@ int init_blocks(const lbm_mc_ctx* c) {
     const auto& q = c->params[0];
     const int64_t nodes = (int64_t)q.nx * q.ny * q.nz;
     return (int)std::min<int64_t>((nodes + 255) / 256, (int64_t)c->cus * 8);
+}
+
+// Both population buffers within the 256 MB last-level cache: the stores write
+// through to it (the next step reads them back from there); above it they
+// stream past the caches.
+bool pops_in_cache(const lbm_mc_ctx* c) {
+    return 2 * c->layout.total * (int64_t)sizeof(float) <= ((int64_t)256 << 20);
+}
+
+// The reverse step keeps four population-sized buffers in play (the state, the
+// two adjoints and the scratch): written-through stores while they fit.
+bool adjoint_in_cache(const lbm_mc_ctx* c) {
+    return 4 * c->layout.total * (int64_t)sizeof(float) <= ((int64_t)256 << 20);
 }
 
 Launch make_launch(lbm_mc_ctx* c, const float* src, float* dst, hipStream_t s) {
@@ -775,10 +798,7 @@ Launch make_launch(lbm_mc_ctx* c, const float* src, float* dst, hipStream_t s) {
     L.moving = 0;
     for (const auto& h : c->hlp) L.moving |= h.moving;
     L.eqb = c->hlp[0].eqb;
-    // both population buffers within the 256 MB last-level cache: the stores
-    // write through to it (the next step reads them back from there); above
-    // it they stream past the caches
-    L.wt = 2 * c->layout.total * (int64_t)sizeof(float) <= ((int64_t)256 << 20) ? 1 : 0;
+    L.wt = pops_in_cache(c) ? 1 : 0;
     L.flag = c->dflag;
     L.stream = s;
     return L;
@@ -843,8 +863,7 @@ lbm_mc_status check_flag(lbm_mc_ctx* c) {
 }
 
 // Tiles of the reverse step: 64 columns, one wave per species (64 x 1; in 3-D
-// 32 x 2 where rows of 64 would leave more lanes idle), layers per tile chosen
-// for about eight tiles per compute unit.
+// 32 x 2 where rows of 64 would leave more lanes idle).
 lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const auto& q = c->params[0];
     const bool half = c->DIM == 3 && round_up(q.nx, 32) < round_up(q.nx, 64);
@@ -852,17 +871,31 @@ lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const int nm = c->DIM == 2 ? q.ny : q.nz;
     const int nxb = (q.nx + bx - 1) / bx, nyb = c->DIM == 3 ? (q.ny + by - 1) / by : 1;
     const int64_t cols = (int64_t)nxb * nyb;
-    const int rows = (int)std::max<int64_t>(1, std::min<int64_t>(16, cols * nm / (8 * (int64_t)c->cus)));
+    // Work-groups of the fused pass (one wave per species) a compute unit
+    // holds: three waves per SIMD by registers, but LDS for three work-groups of
+    // three waves in 3-D; two waves per SIMD with four species and in the build
+    // for 2-D lattices that stay in the caches.  Against eight tiles per
+    // compute unit in column order, up to 16 layers, taken before, us per
+    // reverse step: 2048x1024 three species 259 -> 229, 1024x1024 binary 93 ->
+    // 79, 700x300 three species 55 -> 38, 96x96x96 binary 239 -> 212, 96x64x64
+    // quaternary 179 -> 137.
+    const bool two = c->N == 4 || (c->DIM == 2 && adjoint_in_cache(c));
+    const int held = c->DIM == 3 && c->N == 3 ? 3 : 4 * (two ? 2 : 3) / c->N;
+    const int rows = cheapest_rows(c->DIM == 3 ? 16 : 12, (int64_t)c->cus * held,
+                                   [&](int r) { return cols * ((nm + r - 1) / r); });
+    const int nmc = (nm + rows - 1) / rows;
+    // in the order of the step's tiles: neighbours in the cross-section run at
+    // the same time on one XCD and share their halo rows in its L2
     std::vector<Tile> h;
-    for (int xb = 0; xb < nxb; ++xb)
+    for (int mc = 0; mc < nmc; ++mc)
         for (int yb = 0; yb < nyb; ++yb)
-            for (int m0 = 0; m0 < nm; m0 += rows) {
+            for (int xb = 0; xb < nxb; ++xb) {
                 Tile t{};
                 t.lat = 0;
                 t.x0 = xb * bx;
                 t.y0 = yb * by;
-                t.m0 = m0;
-                t.m1 = std::min(nm, m0 + rows);
+                t.m0 = (int)((int64_t)mc * nm / nmc);
+                t.m1 = (int)((int64_t)(mc + 1) * nm / nmc);
                 h.push_back(t);
             }
     HIPCHECK(hipMalloc(&c->adj_tiles, h.size() * sizeof(Tile)));
@@ -959,10 +992,7 @@ Launch adjoint_launch(lbm_mc_ctx* c, const float* f_prev, hipStream_t stream) {
     L.ntiles = L.grid = c->adj_ntiles;
     L.bx = c->adj_bx;
     L.by = c->adj_by;
-    // the reverse step keeps four population-sized buffers in play (the
-    // state, the two adjoints and the scratch): written-through stores while
-    // they fit in the last-level cache
-    L.wt = 4 * c->layout.total * (int64_t)sizeof(float) <= ((int64_t)256 << 20) ? 1 : 0;
+    L.wt = adjoint_in_cache(c) ? 1 : 0;
     return L;
 }
 

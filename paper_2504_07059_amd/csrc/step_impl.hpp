@@ -15,16 +15,6 @@
 
 namespace lbmmc {
 
-// Work-groups are dealt to the eight XCDs round-robin by work-group id.  Map
-// the id to a "virtual" id so that the work-groups on one XCD take a
-// contiguous range of the (spatially ordered) tile list and share its halo
-// rows in their XCD's L2.  Bijective for any grid size G.
-__device__ __forceinline__ int virtual_block(int G) {
-    const int b = blockIdx.x;
-    const int k = b & 7, idx = b >> 3, per = G >> 3, rem = G & 7;
-    return k * per + (k < rem ? k : rem) + idx;
-}
-
 // The tiles of a work-group of a grid that may be smaller than the tile list.
 __device__ __forceinline__ void tile_range(int ntiles, int& t0, int& t1) {
     const int G = gridDim.x, vb = virtual_block(G);
