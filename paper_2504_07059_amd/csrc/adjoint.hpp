@@ -87,7 +87,8 @@ struct VjpFwd {
     float y[NS][NS];
 };
 
-template <int NS>
+// (D: space dimensions; the components beyond it are zero and not computed)
+template <int NS, int D>
 __device__ __forceinline__ void vjp_forward(const float (&rho)[NS], const float (&jm)[NS][3],
                                             const CollConst& C, VjpFwd<NS>& f) {
 #pragma unroll
@@ -95,7 +96,7 @@ __device__ __forceinline__ void vjp_forward(const float (&rho)[NS], const float 
         f.live[s] = fabsf(rho[s]) > kRhoTiny;
         const float cr = f.live[s] ? C.c[s] * rcp_nr(rho[s]) : 0.0f;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) f.ue[s][d] = fmaf(jm[s][d], cr, 0.5f * C.g[d]);
+        for (int d = 0; d < D; ++d) f.ue[s][d] = fmaf(jm[s][d], cr, 0.5f * C.g[d]);
     }
     f.R = 0.0f;
     f.n = 0.0f;
@@ -106,13 +107,14 @@ __device__ __forceinline__ void vjp_forward(const float (&rho)[NS], const float 
     }
     f.iR = rcp_nr(f.R);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) f.U[d] = 0.0f;
+    for (int d = 0; d < D; ++d) f.U[d] = 0.0f;
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) f.U[d] += rho[s] * f.ue[s][d] * f.iR;
+        for (int d = 0; d < D; ++d) f.U[d] += rho[s] * f.ue[s][d] * f.iR;
     tau_solve<NS>(rho, f.R, f.n, C, f.y);
-    f.UU = f.U[0] * f.U[0] + f.U[1] * f.U[1] + f.U[2] * f.U[2];
+    f.UU = f.U[0] * f.U[0] + f.U[1] * f.U[1];
+    if (D == 3) f.UU += f.U[2] * f.U[2];
 }
 
 // Adjoints of the shared intermediates: u, rho, the species densities and
@@ -147,6 +149,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
     constexpr int Q = Lat<LAT>::Q;
     using L = Lat<LAT>;
     const float c = C.c[i], ics = C.inv_cs2[i], itau = C.inv_tau[i], fp = C.fpref[i];
+    constexpr int D = L::DIM;   // (components beyond it are zero)
     const float iR = f.iR;
     // friction V_i = sum_j W_ij (ue_i - ue_j), W_ij = rho_j y_ij / R
     float V[3] = {0.0f, 0.0f, 0.0f};
@@ -155,17 +158,20 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
         if (j == i) continue;
         const float w = rho[j] * f.y[i][j] * iR;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) V[d] += w * (f.ue[i][d] - f.ue[j][d]);
+        for (int d = 0; d < D; ++d) V[d] += w * (f.ue[i][d] - f.ue[j][d]);
     }
     float du[3], Fv[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         du[d] = f.ue[i][d] - f.U[d];
         Fv[d] = rho[i] * C.g[d];
     }
     const float* U = f.U;
-    const float uD = U[0] * du[0] + U[1] * du[1] + U[2] * du[2];
-    const float uV = U[0] * V[0] + U[1] * V[1] + U[2] * V[2];
+    float uD = U[0] * du[0] + U[1] * du[1], uV = U[0] * V[0] + U[1] * V[1];
+    if constexpr (D == 3) {
+        uD += U[2] * du[2];
+        uV += U[2] * V[2];
+    }
     // Every per-direction term of the reverse sweep is lam_a w_a times a
     // polynomial of degree <= 3 in e_a = c (cx, cy, cz): the sweep reduces
     // to the moments of w_a lam_a over the directions.  With integer
@@ -178,7 +184,6 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
     // alpha = itau (1 - ics u.D) + ics u.V, Z = itau D - V:
     //   PM0 = sum w lam P,  PM1 = sum w lam P e,
     //   drho_i += alpha PM0 + ics Z.PM1, and the vector sums below.
-    constexpr int D = L::DIM;
     auto ec = [](int a, int j) { return j == 0 ? L::cx(a) : (j == 1 ? L::cy(a) : L::cz(a)); };
     float n0 = 0.0f, n1[3] = {0.0f, 0.0f, 0.0f}, n2[3][3] = {}, n3[3][3] = {};
 #pragma unroll
@@ -203,7 +208,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
     const float c2 = c * c, c3 = c2 * c;
     float M1[3], M2U[3], M2Z[3], M2F[3], M3UU[3], M3ZU[3], Z[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
+    for (int j = 0; j < D; ++j) {
         Z[j] = fmaf(itau, du[j], -V[j]);
         M1[j] = M2U[j] = M2Z[j] = M2F[j] = M3UU[j] = M3ZU[j] = 0.0f;
     }
@@ -256,7 +261,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
     const float s_uF = -fp * ics * n0;
     float gU[3], gdu[3], gV[3], gF[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
+    for (int j = 0; j < D; ++j) {
         const float a1 = fmaf(ics, M2U[j], M1[j]);
         const float a2 = fmaf(ics, M3ZU[j], M2Z[j]);
         gU[j] = fmaf(fp * ics * ics, M2F[j], ri * ics * fmaf(alpha, a1, ics * a2));
@@ -265,7 +270,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
         gF[j] = fp * ics * a1;
     }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         gU[d] += s_uD * du[d] + s_uV * V[d] + s_uF * Fv[d] + 2.0f * s_UU * U[d];
         gdu[d] += s_uD * U[d];
         gV[d] += s_uV * U[d];
@@ -274,13 +279,13 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
     A.drho[i] += drf;
     // F_i = rho_i g
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         A.drho[i] += gF[d] * C.g[d];
         dg[d] += rho[i] * gF[d];
     }
     // du_i = ue_i - U
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         A.due[i][d] += gdu[d];
         A.dU[d] += gU[d] - gdu[d];
     }
@@ -291,7 +296,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
         const float W = rho[j] * f.y[i][j] * iR;
         float dW = 0.0f;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
+        for (int d = 0; d < D; ++d) {
             dW += gV[d] * (f.ue[i][d] - f.ue[j][d]);
             A.due[i][d] += W * gV[d];
             A.due[j][d] -= W * gV[d];
@@ -304,7 +309,7 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
 
 // Reverse of the mixture velocity, of the cross-relaxation solve and of
 // rho = sum rho_s, n = sum rho_s/M_s: completes A.drho and A.due, adds dL/dK.
-template <int NS>
+template <int NS, int D>
 __device__ __forceinline__ void vjp_mixture(const float (&rho)[NS], const VjpFwd<NS>& f,
                                             const CollConst& C, VjpAcc<NS>& A,
                                             float (&dK)[NS][NS]) {
@@ -313,11 +318,13 @@ __device__ __forceinline__ void vjp_mixture(const float (&rho)[NS], const VjpFwd
 #pragma unroll
     for (int s = 0; s < NS; ++s)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
+        for (int d = 0; d < D; ++d) {
             A.due[s][d] += A.dU[d] * rho[s] * iR;
             A.drho[s] += A.dU[d] * f.ue[s][d] * iR;
         }
-    float dR = A.dR - (A.dU[0] * f.U[0] + A.dU[1] * f.U[1] + A.dU[2] * f.U[2]) * iR;
+    float dUU = A.dU[0] * f.U[0] + A.dU[1] * f.U[1];
+    if (D == 3) dUU += A.dU[2] * f.U[2];
+    float dR = A.dR - dUU * iR;
     // y: both orders of a pair are the same unknown
     float dYs[NS][NS];
 #pragma unroll
@@ -340,18 +347,19 @@ __device__ __forceinline__ void vjp_finish(int s, const float (&rho)[NS], const 
                                            float (&lt)[Lat<LAT>::Q], float (&dg)[3]) {
     constexpr int Q = Lat<LAT>::Q;
     using L = Lat<LAT>;
-    float dj[3];
+    constexpr int D = L::DIM;
+    float dj[3] = {0.0f, 0.0f, 0.0f};
     float drho = A.drho[s];
     const float irho = f.live[s] ? rcp_nr(rho[s]) : 0.0f;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < D; ++d) {
         dg[d] += 0.5f * A.due[s][d];
         dj[d] = A.due[s][d] * irho;
         drho -= A.due[s][d] * (f.ue[s][d] - 0.5f * C.g[d]) * irho;
     }
 #pragma unroll
     for (int a = 0; a < Q; ++a)
-        lt[a] += drho + C.c[s] * (L::cx(a) * dj[0] + L::cy(a) * dj[1] + L::cz(a) * dj[2]);
+        lt[a] += drho + C.c[s] * cdot<LAT>(a, dj[0], dj[1], dj[2]);
 }
 
 // Vector-Jacobian product of the collision at one node, all species:
@@ -361,12 +369,12 @@ __device__ __forceinline__ void collide_vjp(const float (&rho)[NS], const float 
                                             float (&lt)[NS][Lat<LAT>::Q], const CollConst& C,
                                             float (&dK)[NS][NS], float (&dg)[3]) {
     VjpFwd<NS> f;
-    vjp_forward<NS>(rho, jm, C, f);
+    vjp_forward<NS, Lat<LAT>::DIM>(rho, jm, C, f);
     VjpAcc<NS> A;
     vjp_zero<NS>(A);
 #pragma unroll
     for (int i = 0; i < NS; ++i) vjp_species<LAT, NS>(i, rho, f, C, lt[i], A, dg);
-    vjp_mixture<NS>(rho, f, C, A, dK);
+    vjp_mixture<NS, Lat<LAT>::DIM>(rho, f, C, A, dK);
 #pragma unroll
     for (int s = 0; s < NS; ++s) vjp_finish<LAT, NS>(s, rho, f, C, A, lt[s], dg);
 }

@@ -65,11 +65,13 @@ template <int LAT, int NS, int POL>
 struct AdjSplitOp {
     static constexpr int Q = Lat<LAT>::Q;
     static constexpr int NG = NS * (NS - 1) / 2 + 3;
-    static constexpr int KX = 4 + 5 * NS;   // packed contribution floats per species
+    static constexpr int D = Lat<LAT>::DIM;
+    // packed contribution floats per species
+    static constexpr int KX = D + 1 + (D + 2) * NS;
     Buf lam;      // lam_s(t), representation space (this species' view)
     Buf mu;       // scratch, population space (this species' view)
     CollConst C;
-    float (*x1)[4][64];
+    float (*x1)[D + 1][64];
     float (*x2)[KX][64];
     int s, lane;
     bool inside;
@@ -82,13 +84,13 @@ struct AdjSplitOp {
     // FP64 gradient sums of this lane, in registers, or in 3-D and for kThree
     // in LDS.  Every wave holds the same dL/dK: the species-0 wave alone adds
     // it (acck: this lane's element of the work-group's [pairs][64] doubles);
-    // dL/dg is each species' own (accl: of the wave's [3][64] doubles).
+    // dL/dg is each species' own (accl: of the wave's [D][64] doubles).
     // (Three species in 3-D with dL/dg in registers: a fourth work-group per
     // compute unit, but 30 registers spilled; 187 against 166 us per reverse
     // step of 128x96x64.)
     static constexpr int NP = NS * (NS - 1) / 2;
     static constexpr bool kLdsSums = Lat<LAT>::DIM == 3 || kThree;
-    double accr[kLdsSums ? 1 : 3];
+    double accr[kLdsSums ? 1 : D];
     double acckr[kLdsSums ? 1 : NP];
     double* accl;
     double* acck;
@@ -106,7 +108,7 @@ struct AdjSplitOp {
     }
     __device__ __forceinline__ void clear_sums() {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) accg(d) = 0.0;
+        for (int d = 0; d < D; ++d) accg(d) = 0.0;
         if (s == 0) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) accp(k) = 0.0;
@@ -149,14 +151,14 @@ struct AdjSplitOp {
         for (int a = 1; a < Q; ++a) {
             const float v = F[a];
             sf += v;
-            jx += (float)L::cx(a) * v;
-            jy += (float)L::cy(a) * v;
-            jz += (float)L::cz(a) * v;
+            if (L::cx(a) == 1) jx += v; else if (L::cx(a) == -1) jx -= v;
+            if (L::cy(a) == 1) jy += v; else if (L::cy(a) == -1) jy -= v;
+            if (L::cz(a) == 1) jz += v; else if (L::cz(a) == -1) jz -= v;
         }
         x1[s][0][lane] = fmaf(P0, L::inv_w0, sf);
         x1[s][1][lane] = jx;
         x1[s][2][lane] = jy;
-        x1[s][3][lane] = jz;
+        if constexpr (D == 3) x1[s][3][lane] = jz;
         __syncthreads();
         float rho[NS], jm[NS][3];
 #pragma unroll
@@ -164,10 +166,10 @@ struct AdjSplitOp {
             rho[j] = x1[j][0][lane];
             jm[j][0] = x1[j][1][lane];
             jm[j][1] = x1[j][2][lane];
-            jm[j][2] = x1[j][3][lane];
+            jm[j][2] = D == 3 ? x1[j][D == 3 ? 3 : 0][lane] : 0.0f;
         }
         VjpFwd<NS> f;
-        vjp_forward<NS>(rho, jm, C, f);
+        vjp_forward<NS, Lat<LAT>::DIM>(rho, jm, C, f);
         VjpAcc<NS> part;
         vjp_zero<NS>(part);
         float dg[3] = {0.0f, 0.0f, 0.0f};
@@ -182,14 +184,14 @@ struct AdjSplitOp {
         {
             int k = 0;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) x2[s][k++][lane] = part.dU[d];
+            for (int d = 0; d < D; ++d) x2[s][k++][lane] = part.dU[d];
             x2[s][k++][lane] = part.dR;
 #pragma unroll
             for (int j = 0; j < NS; ++j) x2[s][k++][lane] = part.drho[j];
 #pragma unroll
             for (int j = 0; j < NS; ++j)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) x2[s][k++][lane] = part.due[j][d];
+                for (int d = 0; d < D; ++d) x2[s][k++][lane] = part.due[j][d];
 #pragma unroll
             for (int j = 0; j < NS; ++j) x2[s][k++][lane] = row[j];
         }
@@ -200,14 +202,14 @@ struct AdjSplitOp {
         for (int v = 0; v < NS; ++v) {
             int k = 0;
 #pragma unroll
-            for (int d = 0; d < 3; ++d) A.dU[d] += x2[v][k++][lane];
+            for (int d = 0; d < D; ++d) A.dU[d] += x2[v][k++][lane];
             A.dR += x2[v][k++][lane];
 #pragma unroll
             for (int j = 0; j < NS; ++j) A.drho[j] += x2[v][k++][lane];
 #pragma unroll
             for (int j = 0; j < NS; ++j)
 #pragma unroll
-                for (int d = 0; d < 3; ++d) A.due[j][d] += x2[v][k++][lane];
+                for (int d = 0; d < D; ++d) A.due[j][d] += x2[v][k++][lane];
 #pragma unroll
             for (int j = 0; j < NS; ++j) A.dY[v][j] = x2[v][k++][lane];
         }
@@ -216,7 +218,7 @@ struct AdjSplitOp {
         for (int i = 0; i < NS; ++i)
 #pragma unroll
             for (int j = 0; j < NS; ++j) dK[i][j] = 0.0f;
-        vjp_mixture<NS>(rho, f, C, A, dK);
+        vjp_mixture<NS, Lat<LAT>::DIM>(rho, f, C, A, dK);
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
             if (i != s) continue;
@@ -235,7 +237,7 @@ struct AdjSplitOp {
                     for (int j = i + 1; j < NS; ++j, ++k) accp(k) += (double)dK[i][j];
             }
 #pragma unroll
-            for (int d = 0; d < 3; ++d) accg(d) += (double)dg[d];
+            for (int d = 0; d < D; ++d) accg(d) += (double)dg[d];
         }
     }
     // the wave's sums, for the block reduction
@@ -247,7 +249,7 @@ struct AdjSplitOp {
             for (int k = 0; k < NP; ++k) out[k] = accp(k);
         }
 #pragma unroll
-        for (int d = 0; d < 3; ++d) out[NP + d] = accg(d);
+        for (int d = 0; d < 3; ++d) out[NP + d] = d < D ? accg(d < D ? d : 0) : 0.0;
     }
 };
 
@@ -260,9 +262,9 @@ __global__ void __launch_bounds__(256) k_adj_collide(const float* __restrict__ f
                                                      double* __restrict__ gpart) {
     constexpr int DIM = Lat<LAT>::DIM;
     using Op = AdjSplitOp<LAT, NS, POL>;
-    __shared__ float x1[NS][4][64];
+    __shared__ float x1[NS][DIM + 1][64];
     __shared__ float x2[NS][Op::KX][64];
-    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? 3 : 1][64];
+    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? DIM : 1][64];
     __shared__ double ksum[Op::kLdsSums ? Op::NP : 1][64];
     // 3-D: the march's partial sums of every wave
     __shared__ float msum[Lat<LAT>::DIM == 3 ? NS - 1 : 1][2 * kMarDirs<LAT>][64];
@@ -761,7 +763,9 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
 // so the storage transform and its inverse drop out, and mu(t) goes to mu_out.
 // The parameter gradients accumulate as in kernel A.
 // Its two gathers and the collision VJP keep the vector units busy two thirds of
-// the time in 2-D; in 3-D latency bounds it, at few waves.  Asked for three
+// the time in 2-D (vector components beyond the lattice's dimensions are neither
+// computed nor exchanged: 2048x1024 with three species 228 -> 215 us per reverse
+// step); in 3-D latency bounds it, at few waves.  Asked for three
 // waves per SIMD the D3Q19 build takes 168 VGPRs (192 with three species before)
 // and a compute unit holds three work-groups instead of two: 128x96x64 with
 // three species 235 -> 167 us per reverse step, tiles and their order included.
@@ -774,13 +778,13 @@ __global__ void __launch_bounds__(256)
                 const Tile* __restrict__ tiles, int bx, double* __restrict__ gpart) {
     constexpr int DIM = Lat<LAT>::DIM;
     using Op = AdjSplitOp<LAT, NS, POL>;
-    __shared__ float x1[NS][4][64];
+    __shared__ float x1[NS][DIM + 1][64];
     __shared__ float x2[NS][Op::KX][64];
     // the two marches' partial sums of every wave (3-D and the three-wave
     // build)
     constexpr bool HL = Lat<LAT>::DIM == 3 || Op::kThree;
     __shared__ float msum[HL ? NS - 1 : 1][HL ? 4 * kMarDirs<LAT> : 1][64];
-    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? 3 : 1][64];
+    __shared__ double gsum[Op::kLdsSums ? NS : 1][Op::kLdsSums ? DIM : 1][64];
     __shared__ double ksum[Op::kLdsSums ? Op::NP : 1][64];
     const int lane = (int)threadIdx.x;
     const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
@@ -851,9 +855,9 @@ __global__ void __launch_bounds__(256) k_adj_init(const LatParams* __restrict__ 
             for (int a = 1; a < Q; ++a) {
                 const float eu = c * cdot<LAT>(a, -0.5f * C.g[0], -0.5f * C.g[1], -0.5f * C.g[2]);
                 const float fa = L::w(a) * rho[s] * (1.0f + ics * eu);
-                jm[s][0] += (float)L::cx(a) * fa;
-                jm[s][1] += (float)L::cy(a) * fa;
-                jm[s][2] += (float)L::cz(a) * fa;
+                if (L::cx(a)) jm[s][0] += (float)L::cx(a) * fa;
+                if (L::cy(a)) jm[s][1] += (float)L::cy(a) * fa;
+                if (L::cz(a)) jm[s][2] += (float)L::cz(a) * fa;
             }
             float l0 = ldb(Lb[s], 0, own);
 #pragma unroll
