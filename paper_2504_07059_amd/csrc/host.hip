@@ -1569,7 +1569,7 @@ lbm_mc_status lbm_mc_profile_vjp(lbm_mc_ctx* c, const float* state, const double
     if ((const void*)lam == (const void*)state)
         return fail(LBM_MC_ERR_INVALID, "profile_vjp: lam must not alias state");
     HIPCHECK(launch_profile_vjp(c->lattice, c->N, c->dlp, c->hlp[0], state, dxbar, lam,
-                                c->cus * 8, c->stream));
+                                c->cus * 16, c->stream));
     return LBM_MC_OK;
 }
 
