@@ -126,6 +126,15 @@ struct VjpAcc {
     float dY[NS][NS];
 };
 
+// What species i contributes to them, in the few values the others' shares
+// follow from: its friction V_i = sum_j W_ij (u_i - u_j), W_ij = rho_j y_ij/R,
+// reaches u_j by -W_ij gV and rho_j, y_ij and R through dW_j = dL/dW_ij.
+template <int NS>
+struct VjpPart {
+    float dU[3], due[3], gV[3];   // due, drho: of u_i and rho_i themselves
+    float drho, dW[NS];
+};
+
 template <int NS>
 __device__ __forceinline__ void vjp_zero(VjpAcc<NS>& A) {
     A.dU[0] = A.dU[1] = A.dU[2] = 0.0f;
@@ -140,12 +149,12 @@ __device__ __forceinline__ void vjp_zero(VjpAcc<NS>& A) {
 }
 
 // Species i's part (i a compile-time index): lt = dL/df~_i on entry, the
-// direct term (1 - 1/tau_i) dL/df~_i on return; its terms added to A and
-// rho_i dL/dF_i . (dF/dg) to dg.
+// direct term (1 - 1/tau_i) dL/df~_i on return; its contributions in A and
+// rho_i dL/dF_i . (dF/dg) added to dg.
 template <int LAT, int NS>
 __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const VjpFwd<NS>& f,
                                             const CollConst& C, float (&lt)[Lat<LAT>::Q],
-                                            VjpAcc<NS>& A, float (&dg)[3]) {
+                                            VjpPart<NS>& A, float (&dg)[3]) {
     constexpr int Q = Lat<LAT>::Q;
     using L = Lat<LAT>;
     const float c = C.c[i], ics = C.inv_cs2[i], itau = C.inv_tau[i], fp = C.fpref[i];
@@ -276,34 +285,54 @@ __device__ __forceinline__ void vjp_species(int i, const float (&rho)[NS], const
         gV[d] += s_uV * U[d];
         gF[d] += s_uF * U[d];
     }
-    A.drho[i] += drf;
+    A.drho = drf;
     // F_i = rho_i g
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        A.drho[i] += gF[d] * C.g[d];
+        A.drho += gF[d] * C.g[d];
         dg[d] += rho[i] * gF[d];
     }
     // du_i = ue_i - U
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        A.due[i][d] += gdu[d];
-        A.dU[d] += gU[d] - gdu[d];
+        A.due[d] = gdu[d];
+        A.dU[d] = gU[d] - gdu[d];
+        A.gV[d] = gV[d];
     }
     // V_i = sum_j W_ij (ue_i - ue_j)
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
+        A.dW[j] = 0.0f;
         if (j == i) continue;
         const float W = rho[j] * f.y[i][j] * iR;
-        float dW = 0.0f;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-            dW += gV[d] * (f.ue[i][d] - f.ue[j][d]);
-            A.due[i][d] += W * gV[d];
-            A.due[j][d] -= W * gV[d];
+            A.dW[j] += gV[d] * (f.ue[i][d] - f.ue[j][d]);
+            A.due[d] += W * gV[d];
         }
-        A.drho[j] += dW * f.y[i][j] * iR;
-        A.dY[i][j] += dW * rho[j] * iR;
-        A.dR -= dW * W * iR;
+    }
+}
+
+// Species i's contributions added to A.
+template <int NS, int D>
+__device__ __forceinline__ void vjp_add(int i, const float (&rho)[NS], const VjpFwd<NS>& f,
+                                        const VjpPart<NS>& p, VjpAcc<NS>& A) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        A.dU[d] += p.dU[d];
+        A.due[i][d] += p.due[d];
+    }
+    A.drho[i] += p.drho;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        if (j == i) continue;
+        const float W = rho[j] * f.y[i][j] * f.iR;
+        const float dw = p.dW[j] * f.iR;
+#pragma unroll
+        for (int d = 0; d < D; ++d) A.due[j][d] -= W * p.gV[d];
+        A.drho[j] += dw * f.y[i][j];
+        A.dY[i][j] = dw * rho[j];
+        A.dR -= dw * W;
     }
 }
 
@@ -373,7 +402,11 @@ __device__ __forceinline__ void collide_vjp(const float (&rho)[NS], const float 
     VjpAcc<NS> A;
     vjp_zero<NS>(A);
 #pragma unroll
-    for (int i = 0; i < NS; ++i) vjp_species<LAT, NS>(i, rho, f, C, lt[i], A, dg);
+    for (int i = 0; i < NS; ++i) {
+        VjpPart<NS> p;
+        vjp_species<LAT, NS>(i, rho, f, C, lt[i], p, dg);
+        vjp_add<NS, Lat<LAT>::DIM>(i, rho, f, p, A);
+    }
     vjp_mixture<NS, Lat<LAT>::DIM>(rho, f, C, A, dK);
 #pragma unroll
     for (int s = 0; s < NS; ++s) vjp_finish<LAT, NS>(s, rho, f, C, A, lt[s], dg);

@@ -67,7 +67,7 @@ struct AdjSplitOp {
     static constexpr int NG = NS * (NS - 1) / 2 + 3;
     static constexpr int D = Lat<LAT>::DIM;
     // packed contribution floats per species
-    static constexpr int KX = D + 1 + (D + 2) * NS;
+    static constexpr int KX = 3 * D + NS;
     Buf lam;      // lam_s(t), representation space (this species' view)
     Buf mu;       // scratch, population space (this species' view)
     CollConst C;
@@ -85,9 +85,6 @@ struct AdjSplitOp {
     // in LDS.  Every wave holds the same dL/dK: the species-0 wave alone adds
     // it (acck: this lane's element of the work-group's [pairs][64] doubles);
     // dL/dg is each species' own (accl: of the wave's [D][64] doubles).
-    // (Three species in 3-D with dL/dg in registers: a fourth work-group per
-    // compute unit, but 30 registers spilled; 187 against 166 us per reverse
-    // step of 128x96x64.)
     static constexpr int NP = NS * (NS - 1) / 2;
     static constexpr bool kLdsSums = Lat<LAT>::DIM == 3 || kThree;
     double accr[kLdsSums ? 1 : D];
@@ -170,48 +167,44 @@ struct AdjSplitOp {
         }
         VjpFwd<NS> f;
         vjp_forward<NS, Lat<LAT>::DIM>(rho, jm, C, f);
-        VjpAcc<NS> part;
-        vjp_zero<NS>(part);
         float dg[3] = {0.0f, 0.0f, 0.0f};
-        float row[NS];
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            if (i != s) continue;
-            vjp_species<LAT, NS>(i, rho, f, C, lt, part, dg);
-#pragma unroll
-            for (int j = 0; j < NS; ++j) row[j] = part.dY[i][j];
-        }
         {
-            int k = 0;
+            VjpPart<NS> part;
 #pragma unroll
-            for (int d = 0; d < D; ++d) x2[s][k++][lane] = part.dU[d];
-            x2[s][k++][lane] = part.dR;
+            for (int i = 0; i < NS; ++i) {
+                if (i != s) continue;
+                vjp_species<LAT, NS>(i, rho, f, C, lt, part, dg);
+                int k = 0;
 #pragma unroll
-            for (int j = 0; j < NS; ++j) x2[s][k++][lane] = part.drho[j];
+                for (int d = 0; d < D; ++d) {
+                    x2[s][k++][lane] = part.dU[d];
+                    x2[s][k++][lane] = part.due[d];
+                    x2[s][k++][lane] = part.gV[d];
+                }
+                x2[s][k++][lane] = part.drho;
 #pragma unroll
-            for (int j = 0; j < NS; ++j)
-#pragma unroll
-                for (int d = 0; d < D; ++d) x2[s][k++][lane] = part.due[j][d];
-#pragma unroll
-            for (int j = 0; j < NS; ++j) x2[s][k++][lane] = row[j];
+                for (int j = 0; j < NS; ++j)
+                    if (j != i) x2[s][k++][lane] = part.dW[j];
+            }
         }
         __syncthreads();
         VjpAcc<NS> A;
         vjp_zero<NS>(A);
 #pragma unroll
         for (int v = 0; v < NS; ++v) {
+            VjpPart<NS> part;
             int k = 0;
 #pragma unroll
-            for (int d = 0; d < D; ++d) A.dU[d] += x2[v][k++][lane];
-            A.dR += x2[v][k++][lane];
-#pragma unroll
-            for (int j = 0; j < NS; ++j) A.drho[j] += x2[v][k++][lane];
+            for (int d = 0; d < D; ++d) {
+                part.dU[d] = x2[v][k++][lane];
+                part.due[d] = x2[v][k++][lane];
+                part.gV[d] = x2[v][k++][lane];
+            }
+            part.drho = x2[v][k++][lane];
 #pragma unroll
             for (int j = 0; j < NS; ++j)
-#pragma unroll
-                for (int d = 0; d < D; ++d) A.due[j][d] += x2[v][k++][lane];
-#pragma unroll
-            for (int j = 0; j < NS; ++j) A.dY[v][j] = x2[v][k++][lane];
+                if (j != v) part.dW[j] = x2[v][k++][lane];
+            vjp_add<NS, D>(v, rho, f, part, A);
         }
         float dK[NS][NS];
 #pragma unroll
@@ -765,10 +758,13 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
 // Its two gathers and the collision VJP keep the vector units busy two thirds of
 // the time in 2-D (vector components beyond the lattice's dimensions are neither
 // computed nor exchanged: 2048x1024 with three species 228 -> 215 us per reverse
-// step); in 3-D latency bounds it, at few waves.  Asked for three
-// waves per SIMD the D3Q19 build takes 168 VGPRs (192 with three species before)
-// and a compute unit holds three work-groups instead of two: 128x96x64 with
-// three species 235 -> 167 us per reverse step, tiles and their order included.
+// step); in 3-D latency bounds it, at few waves.  Asked for three waves per SIMD
+// the D3Q19 build takes 168 VGPRs (192 with three species before) and a compute
+// unit holds more work-groups: 128x96x64 with three species 235 -> 167 us per
+// reverse step, tiles and their order included.  Each species hands on the
+// 3 D + N values that the others' shares follow from, instead of D + 1 +
+// (D + 2) N shares, which saves LDS and arithmetic on the sending side: 216 ->
+// 211 and 166 -> 160 us.
 template <int LAT, int NS, int POL, bool WAVE>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(

@@ -872,16 +872,15 @@ lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const int nxb = (q.nx + bx - 1) / bx, nyb = c->DIM == 3 ? (q.ny + by - 1) / by : 1;
     const int64_t cols = (int64_t)nxb * nyb;
     // Work-groups of the fused pass (one wave per species) a compute unit
-    // holds: three waves per SIMD by registers, but LDS for three work-groups of
-    // three waves in 3-D; two waves per SIMD with four species and in the build
-    // for 2-D lattices that stay in the caches.  Against eight tiles per
+    // holds: three waves per SIMD; two with four species and in the build for
+    // 2-D lattices that stay in the caches.  Against eight tiles per
     // compute unit in column order, up to 16 layers, taken before, us per
     // reverse step: 2048x1024 three species 259 -> 229, 1024x1024 binary 93 ->
     // 79, 700x300 three species 55 -> 38, 96x96x96 binary 239 -> 212, 96x64x64
     // quaternary 179 -> 137.
     const bool two = c->N == 4 || (c->DIM == 2 && adjoint_in_cache(c));
-    const int held = c->DIM == 3 && c->N == 3 ? 3 : 4 * (two ? 2 : 3) / c->N;
-    const int rows = cheapest_rows(c->DIM == 3 ? 16 : 12, (int64_t)c->cus * held,
+    const int rows = cheapest_rows(c->DIM == 3 ? 16 : 12,
+                                   (int64_t)c->cus * (4 * (two ? 2 : 3) / c->N),
                                    [&](int r) { return cols * ((nm + r - 1) / r); });
     const int nmc = (nm + rows - 1) / rows;
     // in the order of the step's tiles: neighbours in the cross-section run at
