@@ -862,11 +862,16 @@ lbm_mc_status check_flag(lbm_mc_ctx* c) {
     return LBM_MC_OK;
 }
 
-// Tiles of the reverse step: 64 columns, one wave per species (64 x 1; in 3-D
-// 32 x 2 where rows of 64 would leave more lanes idle).
+// Tiles of the reverse step: 64 columns, one wave per species: 64 x 1, which
+// the wave form of the gathers can take; in 3-D 32 x 2 where rows of 64 would
+// leave more lanes idle and there are three or four species.  us per reverse
+// step, 32 x 2 against 64 x 1: 96x96x96 three species 200, 237; 160x64x64
+// three 159, 164; 30x100x100 quaternary 133, 181; but binary 96x96x96 212, 130,
+// 90x50x33 44, 35, 20x64x64 37, 32, 220x50x50 143, 90.
 lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const auto& q = c->params[0];
-    const bool half = c->DIM == 3 && round_up(q.nx, 32) < round_up(q.nx, 64);
+    const bool half =
+        c->DIM == 3 && c->N > 2 && round_up(q.nx, 32) < round_up(q.nx, 64);
     const int bx = half ? 32 : 64, by = half ? 2 : 1;
     const int nm = c->DIM == 2 ? q.ny : q.nz;
     const int nxb = (q.nx + bx - 1) / bx, nyb = c->DIM == 3 ? (q.ny + by - 1) / by : 1;
