@@ -47,7 +47,8 @@ struct Tile {
     int32_t lat;
     int32_t x0, y0;
     int32_t m0, m1;
-    int32_t pad[3];
+    int32_t x1;          // strips: end of the columns written
+    int32_t pad[2];
 };
 
 // Shapes of the species-split kernels: bx * by = 64 (one segment of 64
@@ -67,6 +68,8 @@ struct Launch {
     float* dst;
     const LatParams* lp;
     const Tile* tiles;
+    const Tile* strips;  // forcing 2 in one pass: its tiles, or null (density pre-pass)
+    int32_t nstrips;
     int32_t ntiles;
     int32_t grid;        // work-groups launched (== ntiles when not persistent)
     int32_t bx, by;      // work-group shape (columns)

@@ -560,7 +560,9 @@ struct lbm_mc_ctx {
     unsigned* dflag = nullptr;
     // tiles
     Tuning tune;
-    std::vector<Tile> htiles;
+    std::vector<Tile> htiles;    // the tiles, then (one-pass forcing 2) the strips
+    std::vector<int> strip_begin;   // per lattice, and their end; empty: no strips
+    int ntiles = 0;              // without the strips
     Tile* dtiles = nullptr;
     size_t dtiles_cap = 0;
     double* dpartial = nullptr;
@@ -658,6 +660,25 @@ lbm_mc_status run_sequence(lbm_mc_ctx* c, int kind, const void* a, const void* b
     return LBM_MC_OK;
 }
 
+// Forcing 2 in one pass: strips of up to 62 columns.
+int strips(int nx) { return (nx + 61) / 62; }
+
+// One pass in strips, or the density pre-pass and the step over tiles of 64
+// columns: the pass saves about a quarter of the time at equal counts, so it is
+// taken while there are fewer than four strips for three tiles.  us per step,
+// pre-pass against strips: 4096x1024 three species 337, 253; 2048x1024
+// quaternary 242, 185; 1500x300 binary 24.0, 17.7; 200x4 binary 8.6, 7.0;
+// 100x3000 three species 34.8, 26.6; but 64x2000 (two strips for a tile) 16.7, 18.9.
+bool strips_pay(const lbm_mc_params* p, int n_lattices, int dim) {
+    if (p[0].forcing != 2 || dim != 2) return false;
+    int64_t s = 0, t = 0;
+    for (int l = 0; l < n_lattices; ++l) {
+        s += (int64_t)strips(p[l].nx) * p[l].ny;
+        t += (int64_t)((p[l].nx + 63) / 64) * p[l].ny;
+    }
+    return 3 * s < 4 * t;
+}
+
 lbm_mc_status build_tiles(lbm_mc_ctx* c) {
     c->htiles.clear();
     const Tuning& T = c->tune;
@@ -688,6 +709,29 @@ lbm_mc_status build_tiles(lbm_mc_ctx* c) {
                 }
         c->hlp[l].tile_end = (int)c->htiles.size();
     }
+    c->ntiles = (int)c->htiles.size();
+    // strips even in width: one of a single column could miss the third one of
+    // a wall's one-sided difference
+    c->strip_begin.clear();
+    if (strips_pay(c->params.data(), c->L, c->DIM) && T.split && T.bx == 64 && T.by == 1 &&
+        T.persistent == 0) {
+        for (int l = 0; l < c->L; ++l) {
+            const auto& q = c->params[l];
+            const int nxb = strips(q.nx), nmc = (q.ny + T.rows - 1) / T.rows;
+            c->strip_begin.push_back((int)c->htiles.size());
+            for (int mc = 0; mc < nmc; ++mc)
+                for (int xb = 0; xb < nxb; ++xb) {
+                    Tile t{};
+                    t.lat = l;
+                    t.x0 = (int)((int64_t)xb * q.nx / nxb);
+                    t.x1 = (int)((int64_t)(xb + 1) * q.nx / nxb);
+                    t.m0 = (int)((int64_t)mc * q.ny / nmc);
+                    t.m1 = (int)((int64_t)(mc + 1) * q.ny / nmc);
+                    c->htiles.push_back(t);
+                }
+        }
+        c->strip_begin.push_back((int)c->htiles.size());
+    }
     const size_t nt = c->htiles.size();
     if (nt > c->dtiles_cap) {
         if (c->dtiles) (void)hipFree(c->dtiles);
@@ -695,7 +739,7 @@ lbm_mc_status build_tiles(lbm_mc_ctx* c) {
         HIPCHECK(hipMalloc(&c->dtiles, nt * sizeof(Tile)));
         c->dtiles_cap = nt;
     }
-    const size_t np = nt * (size_t)(c->N + 3);
+    const size_t np = (size_t)c->ntiles * (c->N + 3);
     if (np > c->dpartial_cap) {
         if (c->dpartial) (void)hipFree(c->dpartial);
         c->dpartial = nullptr;
@@ -711,16 +755,16 @@ lbm_mc_status build_tiles(lbm_mc_ctx* c) {
     return LBM_MC_OK;
 }
 
-// Layers per tile of least cost: a tile of r layers gathers r + 1 (the halo of
-// its first and last), and the chip holds `cap` work-groups at a time, so a
-// launch of tiles(r) work-groups takes about ceil(tiles(r) / cap) rounds of
-// r + 1 layers.  The shortest of the cheapest.
+// Layers per tile of least cost: a tile of r layers gathers r + halo (1: the
+// halo of its first and last), and the chip holds `cap` work-groups at a time,
+// so a launch of tiles(r) work-groups takes about ceil(tiles(r) / cap) rounds of
+// r + halo layers.  The shortest of the cheapest.
 template <class Tiles>
-int cheapest_rows(int max_rows, int64_t cap, Tiles&& tiles) {
+int cheapest_rows(int max_rows, int halo, int64_t cap, Tiles&& tiles) {
     int best = 1;
     int64_t least = INT64_MAX;
     for (int r = 1; r <= max_rows; ++r) {
-        const int64_t cost = (tiles(r) + cap - 1) / cap * (r + 1);
+        const int64_t cost = (tiles(r) + cap - 1) / cap * (r + halo);
         if (cost < least) {
             least = cost;
             best = r;
@@ -745,13 +789,17 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, i
     // 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary 40, 37.2, 37.9, 42,
     // 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).  Against eight
     // tiles per compute unit, up to 32 layers (16 in 3-D), taken before:
-    // 4096x1024 204 -> 189, 3001x700 with all forcing terms 178 -> 151, 512
-    // tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
-    const int64_t cap = (int64_t)cus * (4 * (dim == 3 ? 4 : 6) / ns);
-    t.rows = cheapest_rows(dim == 3 ? 16 : 6, cap, [&](int r) {
+    // 4096x1024 204 -> 189, 512 tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
+    // (Strips: 4 waves per SIMD and a halo of two layers.  1, 2, 4, 6, 10, 16
+    // layers: 4096x1024 three species 407, 311, 269, 253, 253, 265; 1024x64
+    // quaternary 15.3, 13.5, 17.4, 21, 30, 46.)
+    const bool strip = strips_pay(p, n_lattices, dim);
+    const int64_t cap = (int64_t)cus * (4 * (dim == 3 || strip ? 4 : 6) / ns);
+    t.rows = cheapest_rows(dim == 3 ? 16 : (strip ? 12 : 6), strip ? 2 : 1, cap, [&](int r) {
         int64_t tiles = 0;
         for (int l = 0; l < n_lattices; ++l) {
-            const int64_t cols = (int64_t)((p[l].nx + 63) / 64) * (dim == 3 ? p[l].ny : 1);
+            const int64_t cols = strip ? strips(p[l].nx)
+                                       : (int64_t)((p[l].nx + 63) / 64) * (dim == 3 ? p[l].ny : 1);
             tiles += cols * (((dim == 3 ? p[l].nz : p[l].ny) + r - 1) / r);
         }
         return tiles;
@@ -786,7 +834,11 @@ Launch make_launch(lbm_mc_ctx* c, const float* src, float* dst, hipStream_t s) {
     L.dst = dst;
     L.lp = c->dlp;
     L.tiles = c->dtiles;
-    L.ntiles = (int)c->htiles.size();
+    L.ntiles = c->ntiles;
+    if (!c->strip_begin.empty()) {
+        L.strips = c->dtiles + c->ntiles;
+        L.nstrips = c->strip_begin.back() - c->ntiles;
+    }
     L.grid = c->tune.persistent > 0 ? std::min(L.ntiles, c->tune.persistent) : L.ntiles;
     L.bx = c->tune.bx;
     L.by = c->tune.by;
@@ -811,6 +863,10 @@ lbm_mc_status launch_one(lbm_mc_ctx* c, const float* src, float* dst, hipStream_
             Launch L = make_launch(c, src, dst, s);
             L.tiles = c->dtiles + c->hlp[l].tile_begin;
             L.ntiles = c->hlp[l].tile_end - c->hlp[l].tile_begin;
+            if (!c->strip_begin.empty()) {
+                L.strips = c->dtiles + c->strip_begin[l];
+                L.nstrips = c->strip_begin[l + 1] - c->strip_begin[l];
+            }
             L.grid = L.ntiles;
             HIPCHECK(launch_step(c->lattice, c->N, L));
         }
@@ -884,7 +940,7 @@ lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     // 79, 700x300 three species 55 -> 38, 96x96x96 binary 239 -> 212, 96x64x64
     // quaternary 179 -> 137.
     const bool two = c->N == 4 || (c->DIM == 2 && adjoint_in_cache(c));
-    const int rows = cheapest_rows(c->DIM == 3 ? 16 : 12,
+    const int rows = cheapest_rows(c->DIM == 3 ? 16 : 12, 1,
                                    (int64_t)c->cus * (4 * (two ? 2 : 3) / c->N),
                                    [&](int r) { return cols * ((nm + r - 1) / r); });
     const int nmc = (nm + rows - 1) / rows;
@@ -1436,7 +1492,7 @@ lbm_mc_status lbm_mc_autotune(lbm_mc_ctx* c, int32_t reps, double* best_us) {
         if (st != LBM_MC_OK) return st;
         // a persistent grid no smaller than the tile list is the same launch
         // as the non-persistent candidate of the same shape
-        if (t.persistent > 0 && t.persistent >= (int)c->htiles.size()) continue;
+        if (t.persistent > 0 && t.persistent >= c->ntiles) continue;
         for (int i = 0; i < 2; ++i) {
             st = launch_one(c, c->cur, c->prev, c->stream);
             if (st != LBM_MC_OK) return st;

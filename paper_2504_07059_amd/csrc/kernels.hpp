@@ -107,9 +107,12 @@ __device__ __forceinline__ float ldb(const Buf& b, int p, unsigned vb) {
 // and reads none of them back).  kStoreNT, the non-temporal (`nt`) policy,
 // suits states larger than the last-level cache; kStoreWT, device scope
 // (`sc1`: written through to the last-level cache), suits states that fit in
-// it and are read again from there by the next step.  Either changes no value
-// and no coherence rule; the host picks one per context by the size of the
-// two population buffers.
+// it and are read again from there by the next step.  kStoreWB, written back
+// from the L2, is for stores that do not fill their lines (k_step_strip: two
+// strips write the line between them).  Neither changes a value or a coherence
+// rule; the host picks one per context by the size of the two population
+// buffers.
+constexpr int kStoreWB = 0;
 constexpr int kStoreNT = 2;
 constexpr int kStoreWT = 16;
 template <int POL = kStoreNT>

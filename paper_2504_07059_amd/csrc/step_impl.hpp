@@ -184,6 +184,18 @@ struct SplitOp {
     unsigned skip;
     __device__ __forceinline__ void operator()(float P0, float (&F)[Q], int m, unsigned own) {
         constexpr int DIM = Lat<LAT>::DIM;
+        float gi[3] = {};
+        if constexpr (FRC == 2) {
+            const float* f = dens;
+            field_grad<DIM>([&](int64_t j) { return f[j]; }, P->nx, P->ny, P->nz, P->wall_mask,
+                            x, DIM == 2 ? m : y, DIM == 2 ? 0 : m, gi);
+        }
+        node(P0, F, gi, m, own);
+    }
+    // the collision of layer m (FRC 2: gi, the gradient of this species' density)
+    __device__ __forceinline__ void node(float P0, float (&F)[Q], const float (&gi)[3], int m,
+                                         unsigned own) {
+        constexpr int DIM = Lat<LAT>::DIM;
         float g[3];
         node_accel<LAT, EXT == 1>(accel, *P, C.g, dense_node<LAT>(*P, x, y, m), g);
         float rho_s, dlt_s, ue_s[3];
@@ -192,9 +204,8 @@ struct SplitOp {
         X[s * 64 + lane] = make_float4(rho_s, ue_s[0], ue_s[1], ue_s[2]);
         Grads gd{};
         if constexpr (FRC == 2) {
-            const float* f = dens;
-            field_grad<DIM>([&](int64_t j) { return f[j]; }, P->nx, P->ny, P->nz, P->wall_mask,
-                            x, DIM == 2 ? m : y, DIM == 2 ? 0 : m, gd.gi);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) gd.gi[d] = gi[d];
             xgr[(m & 1) * xstride + s * 64 + lane] =
                 make_float4(gd.gi[0], gd.gi[1], gd.gi[2], 0.0f);
         }
@@ -342,6 +353,121 @@ __device__ __forceinline__ float streamed_density(float P0, const float (&F)[Lat
 #pragma unroll
     for (int a = 1; a < Lat<LAT>::Q; ++a) sf += F[a];
     return fmaf(P0, Lat<LAT>::inv_w0, sf);
+}
+
+// Forcing 2 on 2-D lattices in one pass, without the density fields: one wave
+// per species marches the layers of a strip of up to 62 columns with the column
+// beyond either end in its outer lanes, forms each layer's density as it is
+// gathered, and collides a layer once the next one's density is there.  The x
+// differences are taken across lanes, the y differences over the march.  Bound by
+// the vector units (two thirds busy) and by the populations read and written: the
+// strip costs two columns of 64 and a layer more per tile, the pre-pass a second
+// read of all of them.  The stores are written back from the L2, where strips
+// share the line between them (3001x700 three species 132 us per step, 136
+// non-temporal).  Against the pre-pass and the step: 3001x700 155 -> 132, 4096x1024
+// 337 -> 253, 777x101 quaternary with a force field 16.5 -> 14.5.
+template <int NS, int EXT, int POL>
+__global__ void __launch_bounds__(64 * NS) __attribute__((amdgpu_waves_per_eu(3)))
+    k_step_strip(const float* __restrict__ src, float* __restrict__ dst,
+                 const LatParams* __restrict__ lps, const Tile* __restrict__ tiles, int ntiles,
+                 int one, const float* __restrict__ accel, unsigned* __restrict__ flag) {
+    constexpr int LAT = 0, Q = Lat<LAT>::Q;
+    constexpr bool HL = kSplitLdsMarch<LAT, POL>;
+    // [2][NS][64] exchanged moments, [2][NS][64] density gradients, marching sums
+    extern __shared__ float4 smem[];
+    const int lane = (int)threadIdx.x;
+    const int s = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+    const int t = virtual_block(ntiles);
+    const Tile T = tiles[t];
+    const LatParams& P = lps[tile_lattice(tiles, t, one)];
+    const GatherConst G = gather_const(P, 2);
+    // lane l holds column x0 - 1 + l: wrapped, or at an x wall a lane whose
+    // reads return 0; lanes past the strip's right neighbour hold anything
+    const int nx = P.nx, nm = P.ny, wx = -(P.wall_mask & 1);
+    auto column = [&](int c) {
+        const int j = c < 0 ? c + nx : (c >= nx ? c - nx : c);
+        return min(max(j, 0), nx - 1);
+    };
+    const int c0 = T.x0 - 1, c = c0 + lane;
+    const int x = column(c);
+    WaveGeom w = wave_geom<LAT>(G, 0, x, 0, wx != 0 && (c < 0 || c >= nx));
+    w.xl = wx != 0 && c0 < 1 ? kSolid : (unsigned)column(c0 - 1) * 4u;
+    w.xr = wx != 0 && c0 + 64 >= nx ? kSolid : (unsigned)column(c0 + 64) * 4u;
+    const bool inside = lane > 0 && c < T.x1;
+    const float L[3] = {P.lam[s][0], P.lam[s][1], P.lam[s][2]};
+    SplitOp<LAT, NS, 2, EXT, POL> op{species_buf<LAT>(dst + P.base, P.plane, s),
+                                     coll_const(P),
+                                     SpeciesConst{P.c[s], P.inv_cs2[s], P.inv_tau[s], P.fpref[s],
+                                                  P.kdiff[s], P.cs2[s]},
+                                     smem, smem + 2 * NS * 64, NS * 64, s, lane, inside, false,
+                                     nullptr, &P, x, 0, accel, inside ? 0u : kSolid};
+    const Buf B = species_buf<LAT>(src + P.base, P.plane, s);
+    FwdWave<LAT, HL, true> fw{B, G, w, s};
+    if constexpr (HL)
+        fw.h.acc = reinterpret_cast<float*>(smem + 4 * NS * 64) + s * 2 * kMarDirs<LAT> * 64 + lane;
+    // The layers gathered, g0 .. g1, around those collided, m0 .. m1 - 1: a
+    // neighbour on either side, where the lattice ends at a wall the three of
+    // the one-sided difference (its third one from below by a march of its
+    // own, so that every layer is collided one step after it is gathered).
+    const bool wm = w.g.wm != 0;
+    const bool low = wm && T.m0 == 0;
+    int g0 = T.m0 - 1, g1 = T.m1;
+    if (wm) {
+        g1 = min(g1, nm - 1);
+        if (T.m1 == nm) g0 = min(g0, nm - 3);
+        g0 = max(g0, 0);
+    }
+    auto layer = [&](int k) { return k < 0 ? k + nm : (k >= nm ? k - nm : k); };
+    float P0 = 0.0f, F[Q] = {};                             // layer k - 1
+    float rmm = 0.0f, rm = 0.0f, rc = 0.0f, rp = 0.0f;      // densities of k-3 .. k
+    float r2 = 0.0f;                                        // of layer 2 (low)
+    for (int part = low ? 0 : 1; part < 2; ++part) {
+        const int ka = part ? g0 : 2, kg = part ? g1 : 2, kb = part ? T.m1 : 2;
+        fw.begin_loads(layer(ka));
+        fw.begin(L, layer(ka));
+        if (ka < kg) fw.next_lanes();
+        for (int k = ka; k <= kb; ++k) {
+            float Pn = 0.0f, Fn[Q] = {};
+            if (k <= kg) {
+                const int m = layer(k);
+                fw.layer(L, m, k == ka, Pn, Fn);
+                const Sides sd = wall_sides<LAT>(G, w.g, m);
+                if (sd.any) {
+                    const unsigned own = layer_off(w.g, m);
+                    if (s == 0)
+                        wall_returns<LAT, true>(fresh(B), G, L, own, sd, Pn, Fn);
+                    else
+                        wall_returns<LAT, false>(fresh(B), G, L, own, sd, Pn, Fn);
+                }
+                if (k + 1 <= kg) fw.load(layer(k + 1));
+            }
+            rmm = rm;
+            rm = rc;
+            rc = rp;
+            rp = streamed_density<LAT>(Pn, Fn);
+            if (part == 0) {
+                r2 = rp;
+            } else if (k > T.m0) {
+                const int m = k - 1;
+                // the differences of axis_diff
+                const float xm = __shfl(rc, lane - 1), xp = __shfl(rc, lane + 1);
+                float gi[3] = {0.5f * (xp - xm), 0.5f * (rp - rm), 0.0f};
+                if (wx != 0 && (c0 < 0 || T.x1 == nx)) {
+                    const float xmm = __shfl(rc, lane - 2), xpp = __shfl(rc, lane + 2);
+                    const float lo = 0.5f * (fmaf(4.0f, xp, -3.0f * rc) - xpp);
+                    const float hi = 0.5f * (fmaf(3.0f, rc, xmm) - 4.0f * xm);
+                    gi[0] = x == 0 ? lo : (x == nx - 1 ? hi : gi[0]);
+                }
+                if (wm && m == 0) gi[1] = 0.5f * (fmaf(4.0f, rp, -3.0f * rc) - r2);
+                else if (wm && m == nm - 1) gi[1] = 0.5f * (fmaf(3.0f, rc, rmm) - 4.0f * rm);
+                op.node(P0, F, gi, m, layer_off(w.g, m));
+            }
+            P0 = Pn;
+#pragma unroll
+            for (int a = 0; a < Q; ++a) F[a] = Fn[a];
+        }
+    }
+    if (op.bad) atomicOr(flag, 1u);
 }
 
 template <int LAT, int NS>
@@ -889,6 +1015,24 @@ hipError_t launch_step_ns(const Launch& L) {
         } else {
             if (FRC == 2) {
                 if (!L.dens) return hipErrorInvalidValue;
+                if constexpr (LAT == 0 && FRC == 2) {
+                    if (L.strips) {
+                        auto strip = [&](auto pol) {
+                            constexpr int POL = decltype(pol)::value;
+                            const size_t lds =
+                                4 * (size_t)NS * 64 * sizeof(float4) +
+                                (kSplitLdsMarch<LAT, POL>
+                                     ? (size_t)NS * 2 * kMarDirs<LAT> * 64 * sizeof(float)
+                                     : 0);
+                            hipLaunchKernelGGL((k_step_strip<NS, EXT, POL>), dim3(L.nstrips),
+                                               dim3(64, NS), lds, L.stream, L.src, L.dst, L.lp,
+                                               L.strips, L.nstrips, L.one, L.accel, L.flag);
+                            return hipGetLastError();
+                        };
+                        return L.wt ? strip(std::integral_constant<int, kStoreWT>{})
+                                    : strip(std::integral_constant<int, kStoreWB>{});
+                    }
+                }
                 // (the force does not enter the densities)
                 hipError_t e;
                 if (L.split) {
