@@ -415,7 +415,10 @@ Verdict check_lattice(const lbm_mc_params& q, int l, const double* xl, int threa
     };
     constexpr int kGroup = 64;
     std::vector<Group> groups((comps.size() + kGroup - 1) / kGroup);
-    parallel_for((int64_t)groups.size(), threads, [&](int64_t gi) {
+    // (threads cost a process that has just begun them some 12 us in its next
+    // calls as well: below a millisecond of work they are not worth it)
+    const int eig_threads = comps.size() < 1024 ? 1 : threads;
+    parallel_for((int64_t)groups.size(), eig_threads, [&](int64_t gi) {
         Group& G = groups[gi];
         const size_t end = std::min(comps.size(), (size_t)(gi + 1) * kGroup);
         const double ts[4] = {0.0, 0.25, 0.5, 0.75};

@@ -16,6 +16,7 @@
 // fixed order.  The result does not depend on timing (no atomics).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 
@@ -86,8 +87,9 @@ __global__ void __launch_bounds__(64) k_profile_part(const float* __restrict__ s
     for (int i = 0; i < NS; ++i) part[((int64_t)c * NS + i) * P.nx + x] = acc[i];
 }
 
-// xbar[i * nx + x] = (sum over chunks) / rows: wave w of the 16 adds chunks w,
-// w + 16, ... of 64 sums, then the waves' parts are added in wave order.  Bound
+// xbar[i * nx + x] = (sum over chunks) / rows: wave w of the W (up to 16, a wave
+// for every four chunks) adds chunks w, w + W, ... of 64 sums, then the waves'
+// parts are added in wave order.  Bound
 // by the latency of the chain of loads: with one thread per sum and up to 2048
 // chunks it took 258 us for the profile of a 128x96x64 box (512 sums, 1024
 // chunks), as long as the reads of the state; now 11 us.
@@ -99,17 +101,17 @@ __global__ void __launch_bounds__(1024) k_profile_sum(const LatParams* __restric
     const int lane = (int)threadIdx.x, w = (int)threadIdx.y;
     const int64_t total = (int64_t)ns * P.nx;
     const int64_t k = (int64_t)blockIdx.x * 64 + lane;
+    const int W = (int)blockDim.y;
     double v = 0.0;
     if (k < total) {
 #pragma unroll 8
-        for (int c = w; c < nchunks; c += 16) v += part[(int64_t)c * total + k];
+        for (int c = w; c < nchunks; c += W) v += part[(int64_t)c * total + k];
     }
     red[w][lane] = v;
     __syncthreads();
     if (w != 0 || k >= total) return;
     v = 0.0;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v += red[j][lane];
+    for (int j = 0; j < W; ++j) v += red[j][lane];
     xbar[k] = v / ((double)P.ny * (double)P.nz);
 }
 
@@ -194,7 +196,8 @@ hipError_t launch_profile(int lattice, int ns, const LatParams* lp, const LatPar
     });
     if (e != hipSuccess) return e;
     const int64_t total = (int64_t)ns * h.nx;
-    hipLaunchKernelGGL(k_profile_sum, dim3((unsigned)((total + 63) / 64)), dim3(64, 16), 0, st, lp,
+    const int W = std::max(1, std::min(16, nchunks / 4));
+    hipLaunchKernelGGL(k_profile_sum, dim3((unsigned)((total + 63) / 64)), dim3(64, W), 0, st, lp,
                        ns, nchunks, part, xbar);
     return hipGetLastError();
 }
