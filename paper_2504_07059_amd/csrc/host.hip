@@ -1225,7 +1225,15 @@ static lbm_mc_status init_impl(const lbm_mc_params* p, int32_t n_lattices, const
     // default execution shape, or a cached autotuned one
     Tuning t = default_tuning(p, n_lattices, c->DIM, c->N, c->cus);
     if (lattice_has_eq(p[0])) {
-        t.split = 0;   // the equilibrium boundary runs one thread per column
+        // The equilibrium boundary runs one thread per column, in short tiles: a
+        // layer at a wall takes several times one inside (3001x700 three species,
+        // 1, 2, 4, 8 layers: 133, 128, 145, 196 us per step; 512x512 binary 18,
+        // 22, 35, 60).
+        t.split = 0;
+        int64_t layers = 0;
+        for (int l = 0; l < n_lattices; ++l)
+            layers += (int64_t)((p[l].nx + 63) / 64) * p[l].ny * p[l].nz;
+        t.rows = layers > 32 * (int64_t)c->cus ? 2 : 1;
     } else {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(
