@@ -828,9 +828,9 @@ __global__ void __launch_bounds__(256) k_adj_init(const LatParams* __restrict__ 
     const LatParams& P = lps[0];
     const int64_t nodes = (int64_t)P.nx * P.ny * P.nz;
     const CollConst C = coll_const(P);
-    Buf Lb[NS];
+    SpanBuf Lb[NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) Lb[s] = species_buf<LAT>(lam + P.base, P.plane, s);
+    for (int s = 0; s < NS; ++s) Lb[s] = species_span<LAT>(lam + P.base, P.plane, s);
     double acc[NG];
 #pragma unroll
     for (int q = 0; q < NG; ++q) acc[q] = 0.0;

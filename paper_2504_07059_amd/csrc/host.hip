@@ -1227,8 +1227,8 @@ static lbm_mc_status init_impl(const lbm_mc_params* p, int32_t n_lattices, const
     if (lattice_has_eq(p[0])) {
         // The equilibrium boundary runs one thread per column, in short tiles: a
         // layer at a wall takes several times one inside (3001x700 three species,
-        // 1, 2, 4, 8 layers: 133, 128, 145, 196 us per step; 512x512 binary 18,
-        // 22, 35, 60).
+        // 1, 2, 4, 8 layers: 116, 107, 112, 129 us per step; 512x512 binary 11.9,
+        // 13.0, 18.3, 29.8).
         t.split = 0;
         int64_t layers = 0;
         for (int l = 0; l < n_lattices; ++l)

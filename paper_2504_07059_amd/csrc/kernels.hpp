@@ -32,7 +32,8 @@
 // node as a 32-bit per-lane byte offset, so no per-load 64-bit address
 // arithmetic is needed (each species' Q planes stay below 2 GiB; a buffer
 // holds up to 4 of them).  The plane is not a scalar offset of the
-// instruction: one takes the vector memory pipe 9 cycles instead of 5.
+// instruction: one takes the vector memory pipe 9 cycles instead of 5.  (Where a
+// thread holds every species it is: see SpanBuf.)
 //
 // For every node the gather hands over, per species s:
 //   P0[s]     the stored rest population at the node (it does not stream),
@@ -83,6 +84,29 @@ __device__ __forceinline__ Buf species_buf(const float* lattice, int64_t plane, 
     return make_buf(lattice + (int64_t)s * Q * plane, (int64_t)Q * plane, plane);
 }
 
+// The same view with one buffer resource over the species' planes and the plane
+// as the instruction's scalar offset, for the kernels in which a thread holds
+// every species: N Q resources do not fit the scalar registers there, and the
+// compiler keeps what does not fit in lanes of VGPRs, four moves for each load that
+// needs one (three species at the equilibrium boundary: 1311 scalars spilled, 29
+// with this view).  us with resources per plane and with this view: a step with
+// the equilibrium boundary 1024x64 three species 17.0, 11.0, 96x48x40 125, 44;
+// with moving walls, 1024x64 in tiles of 8 rows, 69, 50; with resting walls 33.5,
+// 26.2; the initial state's VJP on 128x64x64 with four species 149, 115.
+struct SpanBuf {
+    __amdgpu_buffer_rsrc_t r;
+    int pb;             // bytes per plane
+};
+
+template <int LAT>
+__device__ __forceinline__ SpanBuf species_span(const float* lattice, int64_t plane, int s) {
+    constexpr int Q = Lat<LAT>::Q;
+    return SpanBuf{__builtin_amdgcn_make_buffer_rsrc(
+                       const_cast<float*>(lattice + (int64_t)s * Q * plane), (short)0,
+                       (int)(Q * plane * 4), 0x00020000),
+                   (int)(plane * 4)};
+}
+
 // Byte offset that lies beyond any species view (the host keeps every
 // species below 2 GiB): a raw buffer load at it is range-checked and returns
 // 0, which is exactly the contribution of a solid (beyond-the-wall) source.
@@ -103,6 +127,10 @@ __device__ __forceinline__ float ldb(const Buf& b, int p, unsigned vb) {
     return __builtin_bit_cast(
         float, __builtin_amdgcn_raw_buffer_load_b32(plane_rsrc(b, p), (int)vb, 0, 0));
 }
+__device__ __forceinline__ float ldb(const SpanBuf& b, int p, unsigned vb) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)vb, p * b.pb, 0));
+}
 // Cache policy of the population stores (a launch writes every value once
 // and reads none of them back).  kStoreNT, the non-temporal (`nt`) policy,
 // suits states larger than the last-level cache; kStoreWT, device scope
@@ -119,6 +147,11 @@ template <int POL = kStoreNT>
 __device__ __forceinline__ void stb(const Buf& b, int p, unsigned vb, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), plane_rsrc(b, p),
                                           (int)vb, 0, POL);
+}
+template <int POL = kStoreNT>
+__device__ __forceinline__ void stb(const SpanBuf& b, int p, unsigned vb, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), b.r, (int)vb,
+                                          p * b.pb, POL);
 }
 
 // Neighbour index i+k (k = -1, +1) on an axis of n nodes: wrapped when periodic
@@ -180,8 +213,8 @@ struct RhoLayer {
 
 // Cross-section pass of plane p of direction components (q0, q1) around byte
 // offset `cen`.
-template <int LAT>
-__device__ __forceinline__ float hpass_load(const Buf& b, int p, int q0, int q1, unsigned cen,
+template <int LAT, class View>
+__device__ __forceinline__ float hpass_load(const View& b, int p, int q0, int q1, unsigned cen,
                                             const Col& c, const float* L) {
     const W3 wx = wsel(q0, L);
     auto row = [&](unsigned r) {
@@ -196,8 +229,8 @@ __device__ __forceinline__ float hpass_load(const Buf& b, int p, int q0, int q1,
     return v;
 }
 
-template <int LAT>
-__device__ __forceinline__ RhoLayer rho_load(const Buf& b, int p, unsigned cen, const Col& c) {
+template <int LAT, class View>
+__device__ __forceinline__ RhoLayer rho_load(const View& b, int p, unsigned cen, const Col& c) {
     RhoLayer r;
     r.c = ldb(b, p, cen);
     r.dxm = ldb(b, p, oadd(cen, c.bxm)) - r.c;
@@ -287,10 +320,11 @@ struct Sides {
 // interpolation, the tensor product in 3-D), so f_a(O) gains
 // w_a sum over solid k of Lambda_k(c_a) rho_s(k).  Densities from the stored
 // form: rho = P0/w_0 + sum_{a>0} g_a.
-template <int LAT>
-__device__ __forceinline__ void eq_wall_terms(const Buf& B, const GatherConst& G, const ColGeom& g,
-                                              int pb0, const float* L, unsigned own, int m,
-                                              const Sides& sd, float (&F)[Lat<LAT>::Q]) {
+template <int LAT, bool BATCH, class View>
+__device__ __forceinline__ void eq_wall_terms(const View& B, const GatherConst& G,
+                                              const ColGeom& g, int pb0, const float* L,
+                                              unsigned own, int m, const Sides& sd,
+                                              float (&F)[Lat<LAT>::Q]) {
     using Fr = Frame<LAT>;
     using La = Lat<LAT>;
     constexpr int Q = La::Q;
@@ -313,9 +347,14 @@ __device__ __forceinline__ void eq_wall_terms(const Buf& B, const GatherConst& G
                 unsigned cl = (km != 0 && !solm) ? layer_off(g, nbr(m, km, G.nm, g.wm)) : own;
                 if (kx != 0 && !solx) cl += kx < 0 ? g.col.bxm : g.col.bxp;
                 if (k1 != 0 && !sol1) cl += k1 < 0 ? g.col.bym : g.col.byp;
-                float rho = ldb(B, pb0, cl) * iw0;
+                float v[Q];
 #pragma unroll
-                for (int b = 1; b < Q; ++b) rho += ldb(B, pb0 + b, cl);
+                for (int b = 0; b < Q; ++b) v[b] = ldb(B, pb0 + b, cl);
+                // (one round trip, not one for each)
+                if constexpr (BATCH) __builtin_amdgcn_sched_barrier(0);
+                float rho = v[0] * iw0;
+#pragma unroll
+                for (int b = 1; b < Q; ++b) rho += v[b];
 #pragma unroll
                 for (int a = 1; a < Q; ++a) {
                     if ((Fr::p0(a) == 0 && kx != 0) || (Fr::p1(a) == 0 && k1 != 0) ||
@@ -452,8 +491,8 @@ __device__ __forceinline__ void heavy_combine(const float* L, const RhoLayer& nx
 // (l+- = lambda_+-1(c)), the Appendix A terms for a single wall.  The node's
 // own planes are read in one batch and the terms taken by selects: one round
 // trip for the waves next to a wall, which set a small lattice's step time.
-template <int LAT, bool FIRST>
-__device__ __forceinline__ void wall_returns(const Buf& B, const GatherConst& G, const float* L,
+template <int LAT, bool FIRST, class View>
+__device__ __forceinline__ void wall_returns(const View& B, const GatherConst& G, const float* L,
                                              unsigned own, const Sides& sd, float rc,
                                              float (&F)[Lat<LAT>::Q]) {
     using La = Lat<LAT>;
@@ -505,28 +544,45 @@ __device__ __forceinline__ void wall_returns(const Buf& B, const GatherConst& G,
 // source reads as 0; wall_returns (or, for the equilibrium comparison
 // boundary, eq_wall_terms) puts in what the node gets instead.  lo, hi: the
 // column in layers m-1 and m+1.
-template <int LAT>
-__device__ __forceinline__ void shift_load(const Buf& B, const ColGeom& g, unsigned own,
+template <int LAT, bool BATCH = false, class View>
+__device__ __forceinline__ void shift_load(const View& B, const ColGeom& g, unsigned own,
                                            unsigned lo, unsigned hi, float& P0,
                                            float (&F)[Lat<LAT>::Q]) {
     using Fr = Frame<LAT>;
     using La = Lat<LAT>;
-    const float r0 = ldb(B, 0, own);
-    P0 = r0;
-    F[0] = 0.0f;
-#pragma unroll
-    for (int a = 1; a < La::Q; ++a) {
+    auto source = [&](int a) {
         const int c0 = Fr::p0(a), c1 = Fr::p1(a), cm = Fr::pm(a);
         unsigned src = cm > 0 ? lo : (cm < 0 ? hi : own);
         if (c0 != 0) src = oadd(src, c0 > 0 ? g.col.bxm : g.col.bxp);
         if (c1 != 0) src = oadd(src, c1 > 0 ? g.col.bym : g.col.byp);
-        F[a] = fmaf(La::wr(a), ldb(B, 0, src) - r0, ldb(B, a, src));
+        return src;
+    };
+    const float r0 = ldb(B, 0, own);
+    P0 = r0;
+    F[0] = 0.0f;
+    if constexpr (BATCH && La::DIM == 2) {
+        float ref[La::Q];
+#pragma unroll
+        for (int a = 1; a < La::Q; ++a) {
+            const unsigned src = source(a);
+            ref[a] = ldb(B, 0, src);
+            F[a] = ldb(B, a, src);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 1; a < La::Q; ++a) F[a] = fmaf(La::wr(a), ref[a] - r0, F[a]);
+    } else {
+#pragma unroll
+        for (int a = 1; a < La::Q; ++a) {
+            const unsigned src = source(a);
+            F[a] = fmaf(La::wr(a), ldb(B, 0, src) - r0, ldb(B, a, src));
+        }
     }
 }
 
 // Start the march of a heavier species (B its view) at layer m0.
-template <int LAT, bool HL>
-__device__ __forceinline__ void heavy_begin(const Buf& B, const GatherConst& G, const ColGeom& g,
+template <int LAT, bool HL, class View>
+__device__ __forceinline__ void heavy_begin(const View& B, const GatherConst& G, const ColGeom& g,
                                             const float* L, int m0, Heavy<LAT, HL>& h) {
     using Fr = Frame<LAT>;
     const unsigned cm_ = layer_off(g, nbr(m0, -1, G.nm, g.wm)), c0_ = layer_off(g, m0);
@@ -548,12 +604,33 @@ __device__ __forceinline__ void heavy_begin(const Buf& B, const GatherConst& G, 
 }
 
 // One layer of a heavier species: second-order interpolation, without walls.
-template <int LAT, bool HL>
-__device__ __forceinline__ void heavy_layer(const Buf& B, const ColGeom& g, const float* L,
+template <int LAT, bool BATCH = false, bool HL, class View>
+__device__ __forceinline__ void heavy_layer(const View& B, const ColGeom& g, const float* L,
                                             unsigned own, unsigned nxt, Heavy<LAT, HL>& h,
                                             float& P0, float (&F)[Lat<LAT>::Q]) {
     using Fr = Frame<LAT>;
     float cxm[2] = {0.0f, 0.0f}, cxp[2] = {0.0f, 0.0f};
+    if constexpr (BATCH && Lat<LAT>::DIM == 2) {
+        constexpr int Q = Lat<LAT>::Q;
+        const RhoLayer ref = rho_load<LAT>(B, 0, nxt, g.col);
+        float vm[Q], vz[Q], vp[Q];
+#pragma unroll
+        for (int a = 1; a < Q; ++a) {
+            const unsigned c = Fr::pm(a) != 0 ? nxt : own;
+            vz[a] = ldb(B, a, c);
+            if (Fr::p0(a) == 0) continue;
+            vm[a] = ldb(B, a, oadd(c, g.col.bxm));
+            vp[a] = ldb(B, a, oadd(c, g.col.bxp));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        heavy_combine<LAT>(L, ref, cxm, cxp,
+                           [&](int a) {
+                               const W3 wx = wsel(Fr::p0(a), L);
+                               return Fr::p0(a) == 0 ? vz[a] : xcomb(wx, vm[a], vz[a], vp[a]);
+                           },
+                           h, P0, F);
+        return;
+    }
     if constexpr (Lat<LAT>::DIM == 3) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
@@ -593,36 +670,53 @@ __device__ __forceinline__ Buf fresh(Buf b) {
     return b;
 }
 
+// Whether the joint gather keeps the loads of a species together (BATCH): in 2-D
+// all of a layer's go out before the first of them is used, in 3-D a species'
+// before the next one's.  Left to itself the compiler orders a layer of every
+// species for few live registers, in the kernels that have much of them live
+// across it down to a load or two in flight; the resting walls do better so.  us
+// per step without and with: equilibrium boundary 1024x64 three species 11.0,
+// 8.9; 4096x1024 222, 217; 128x96x64 quaternary 1474, 512 (96x48x40 three
+// species 44, 47: not taken); moving walls 1500x600 three species 57, 41; but
+// resting walls 512x512 binary 19.1, 21.3.
+template <int LAT, int NS, int EXT>
+constexpr bool kBatchLoads = EXT >= 2 && (Lat<LAT>::DIM == 2 || (EXT == 3 && NS == 4));
+
+__device__ __forceinline__ SpanBuf fresh(SpanBuf b) { return b; }
+
 // Forward pull gather of one column through layers [m0, m1), all species
 // (B: the species views); calls op(P0, F, m, own) for every layer m (own:
 // byte offset of the node within a plane).
-template <int LAT, int NS, bool EQ = false, class Op>
-__device__ __forceinline__ void march(const Buf (&B)[NS], const GatherConst& G, int x, int y,
+template <int LAT, int NS, bool EQ = false, bool BATCH = false, class Op>
+__device__ __forceinline__ void march(const SpanBuf (&B)[NS], const GatherConst& G, int x, int y,
                                       int m0, int m1, Op& op) {
     constexpr int Q = Lat<LAT>::Q;
     const ColGeom g = col_geom<LAT>(G, x, y);
     Heavy<LAT> h[NS > 1 ? NS - 1 : 1];
 #pragma unroll
-    for (int s = 1; s < NS; ++s) heavy_begin<LAT>(fresh(B[s]), G, g, G.lam[s], m0, h[s - 1]);
+    for (int s = 1; s < NS; ++s) heavy_begin<LAT>(B[s], G, g, G.lam[s], m0, h[s - 1]);
     for (int m = m0; m < m1; ++m) {
         const unsigned own = layer_off(g, m);
         const unsigned nxt = layer_off(g, nbr(m, 1, G.nm, g.wm));
         const Sides sd = wall_sides<LAT>(G, g, m);
         float P0[NS], F[NS][Q];
-        shift_load<LAT>(fresh(B[0]), g, own, layer_off(g, nbr(m, -1, G.nm, g.wm)), nxt, P0[0],
-                        F[0]);
+        shift_load<LAT, BATCH>(B[0], g, own, layer_off(g, nbr(m, -1, G.nm, g.wm)), nxt, P0[0],
+                               F[0]);
 #pragma unroll
-        for (int s = 1; s < NS; ++s)
-            heavy_layer<LAT>(fresh(B[s]), g, G.lam[s], own, nxt, h[s - 1], P0[s], F[s]);
+        for (int s = 1; s < NS; ++s) {
+            if constexpr (BATCH) __builtin_amdgcn_sched_barrier(0);
+            heavy_layer<LAT, BATCH>(B[s], g, G.lam[s], own, nxt, h[s - 1], P0[s], F[s]);
+        }
+        if constexpr (BATCH) __builtin_amdgcn_sched_barrier(0);
         if (sd.any) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 if constexpr (EQ)
-                    eq_wall_terms<LAT>(B[s], G, g, 0, G.lam[s], own, m, sd, F[s]);
+                    eq_wall_terms<LAT, BATCH>(B[s], G, g, 0, G.lam[s], own, m, sd, F[s]);
                 else if (s == 0)
-                    wall_returns<LAT, true>(fresh(B[s]), G, G.lam[s], own, sd, P0[s], F[s]);
+                    wall_returns<LAT, true>(B[s], G, G.lam[s], own, sd, P0[s], F[s]);
                 else
-                    wall_returns<LAT, false>(fresh(B[s]), G, G.lam[s], own, sd, P0[s], F[s]);
+                    wall_returns<LAT, false>(B[s], G, G.lam[s], own, sd, P0[s], F[s]);
             }
         }
         op(P0, F, m, own);

@@ -83,7 +83,13 @@ __device__ __forceinline__ void species_grads(const float* dens, const LatParams
 template <int LAT, int NS, int FRC, int EXT, int POL>
 struct StepOp {
     static constexpr int Q = Lat<LAT>::Q;
-    Buf D[NS];               // the destination's species views
+    // The destination's species views.  Stores past the caches take a resource
+    // per plane, formed where a layer uses them: a launch then has many more waves
+    // than the chip holds, and the memory pipe counts (16384x1024 three species,
+    // 256x1, 8 layers: 806 us per step with a scalar offset, 793 so); written
+    // through, the chain of a tile counts (1024x64: 26.3 against 27.2).
+    using DstView = std::conditional_t<POL == kStoreNT, Buf, SpanBuf>;
+    DstView D[NS];
     CollConst C;
     bool bad;
     const float* dens;      // FRC 2: this lattice's density fields
@@ -102,9 +108,10 @@ struct StepOp {
         if (!collide<LAT, NS, FRC>(P0, F, C, g, gi, mw, W)) bad = true;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            stb<POL>(D[s], 0, own, P0[s]);
+            const DstView Ds = fresh(D[s]);
+            stb<POL>(Ds, 0, own, P0[s]);
 #pragma unroll
-            for (int a = 1; a < Q; ++a) stb<POL>(D[s], a, own, F[s][a]);
+            for (int a = 1; a < Q; ++a) stb<POL>(Ds, a, own, F[s][a]);
         }
     }
 };
@@ -130,28 +137,16 @@ __global__ void __launch_bounds__(256) k_step(const float* __restrict__ src, flo
         StepOp<LAT, NS, FRC, EXT, POL> op{{}, coll_const(P), false,
                                     FRC == 2 ? dens + P.field_base * NS : nullptr, &P, x, y,
                                     accel};
-        Buf B[NS];
+        SpanBuf B[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            B[s] = species_buf<LAT>(src + P.base, P.plane, s);
-            op.D[s] = species_buf<LAT>(dst + P.base, P.plane, s);
-        }
-        if constexpr (EXT == 3) {
-            // Work-groups away from the walls take the march without their terms,
-            // whose loads stay in flight together: 4096x1024 three species 369 ->
-            // 244 us per step.
-            const int bx = (int)blockDim.x, by = (int)blockDim.y, w = P.wall_mask;
-            const bool wall =
-                ((w & 1) && (T.x0 == 0 || T.x0 + bx >= P.nx)) ||
-                (DIM == 3 && (w & 2) && (T.y0 == 0 || T.y0 + by >= P.ny)) ||
-                (((w >> (DIM - 1)) & 1) && (T.m0 == 0 || T.m1 == (DIM == 2 ? P.ny : P.nz)));
-            if (wall)
-                march<LAT, NS, true>(B, G, x, y, T.m0, T.m1, op);
+            B[s] = species_span<LAT>(src + P.base, P.plane, s);
+            if constexpr (POL == kStoreNT)
+                op.D[s] = species_buf<LAT>(dst + P.base, P.plane, s);
             else
-                march<LAT, NS, false>(B, G, x, y, T.m0, T.m1, op);
-        } else {
-            march<LAT, NS, false>(B, G, x, y, T.m0, T.m1, op);
+                op.D[s] = species_span<LAT>(dst + P.base, P.plane, s);
         }
+        march<LAT, NS, EXT == 3, kBatchLoads<LAT, NS, EXT>>(B, G, x, y, T.m0, T.m1, op);
         bad = bad || op.bad;
     }
     if (bad) atomicOr(flag, 1u);
@@ -530,9 +525,9 @@ __global__ void __launch_bounds__(256) k_density(const float* __restrict__ src,
         const GatherConst G = gather_const(P, DIM);
         const int64_t nodes = (int64_t)P.nx * P.ny * P.nz;
         DensOp<LAT, NS> op{dens + P.field_base * NS, &P, nodes, x, y};
-        Buf B[NS];
+        SpanBuf B[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) B[s] = species_buf<LAT>(src + P.base, P.plane, s);
+        for (int s = 0; s < NS; ++s) B[s] = species_span<LAT>(src + P.base, P.plane, s);
         march<LAT, NS>(B, G, x, y,
                        T.m0, T.m1, op);
     }
@@ -766,10 +761,10 @@ __global__ void __launch_bounds__(256) k_moments(const float* __restrict__ src,
             }
         } else {
             const GatherConst G = gather_const(P, DIM);
-            Buf B[NS];
+            SpanBuf B[NS];
 #pragma unroll
-            for (int s = 0; s < NS; ++s) B[s] = species_buf<LAT>(lb, P.plane, s);
-            march<LAT, NS, EQ>(B, G, x, y, T.m0, T.m1, op);
+            for (int s = 0; s < NS; ++s) B[s] = species_span<LAT>(lb, P.plane, s);
+            march<LAT, NS, EQ, EQ && kBatchLoads<LAT, NS, 3>>(B, G, x, y, T.m0, T.m1, op);
         }
     }
     // block reduction: wave shuffles, then the waves in a fixed order
