@@ -761,14 +761,16 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
 // step); in 3-D latency bounds it, at few waves.  Asked for three waves per SIMD
 // the D3Q19 build takes 168 VGPRs (192 with three species before) and a compute
 // unit holds more work-groups: 128x96x64 with three species 235 -> 167 us per
-// reverse step, tiles and their order included.  Each species hands on the
+// reverse step, tiles and their order included.  (With three species it spills
+// for that: 10 registers, 44 B of scratch a lane, 7 and 32 B in blocks of 32 x 2.
+// Four take 214 and are left at the two waves that is.)  Each species hands on the
 // 3 D + N values that the others' shares follow from, instead of D + 1 +
 // (D + 2) N shares, which saves LDS and arithmetic on the sending side: 216 ->
 // 211 and 166 -> 160 us.
 template <int LAT, int NS, int POL, bool WAVE>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(
-        AdjSplitOp<LAT, NS, POL>::kThree || Lat<LAT>::DIM == 3 ? 3 : 1)))
+        AdjSplitOp<LAT, NS, POL>::kThree || (Lat<LAT>::DIM == 3 && NS < 4) ? 3 : 1)))
     k_adj_fused(const float* __restrict__ fprev, const float* __restrict__ mu_in,
                 float* __restrict__ mu_out, const LatParams* __restrict__ lps,
                 const Tile* __restrict__ tiles, int bx, double* __restrict__ gpart) {

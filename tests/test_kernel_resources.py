@@ -77,3 +77,21 @@ def test_kernels_with_every_species_in_a_thread(kernels, name):
     bad = {k: v for k, v in _of(kernels, name).items()
            if v["sgpr_spill_count"] > 512 or v["private_segment_fixed_size"] > 0}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("args", ["0, 3, 2, true", "1, 2, 2, true", "1, 3, 2, true",
+                                  "1, 4, 2, true", "1, 4, 16, false"])
+def test_fused_reverse_pass_meets_the_waves_it_asks_for(tmp_path, args):
+    # the compiler warns where a kernel's bound on waves per SIMD cannot be kept
+    from paper_2504_07059_amd import build as B
+    if not os.path.exists(B.HIPCC):
+        pytest.skip("needs hipcc")
+    src = tmp_path / "one.hip"
+    src.write_text('#include "adjoint_impl.hpp"\nnamespace lbmmc {\n'
+                   f"template __global__ void k_adj_fused<{args}>(const float*, const float*, "
+                   "float*, const LatParams*, const Tile*, int, double*);\n}\n")
+    r = subprocess.run([B.HIPCC] + B.FLAGS + ["--cuda-device-only", "-I" + B.CSRC, "-c",
+                                              str(src), "-o", os.devnull],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    assert "failed to meet occupancy" not in r.stderr, r.stderr
