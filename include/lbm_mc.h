@@ -396,8 +396,9 @@ lbm_mc_status lbm_mc_get_tuning(lbm_mc_ctx* ctx, int32_t* block_x, int32_t* bloc
 
 /*
  * Autotuner: time `reps` steps of each candidate execution shape, both
- * variants (state is not advanced: candidates read the current buffer and
- * write the other one) and keep the fastest.  Results are cached per shape class for the process.
+ * variants, the shape in use and the default one among them (state is not
+ * advanced: candidates read the current buffer and write the other one), and keep
+ * the fastest.  Results are cached per shape class for the process.
  * best_us (may be NULL) receives the best time per step in microseconds.
  */
 lbm_mc_status lbm_mc_autotune(lbm_mc_ctx* ctx, int32_t reps, double* best_us);
