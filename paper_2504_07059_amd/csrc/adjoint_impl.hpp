@@ -438,7 +438,7 @@ struct RevRows {
         return ldb(M, a, rev_source<LAT>(col, a, lo, own, nxt));
     }
 };
-// The same rows, loaded ahead (2-D).
+// The same rows in registers (2-D).
 template <int LAT>
 struct RevRaw : WaveRaw<LAT, true> {
     __device__ __forceinline__ float rest() const { return this->v[0]; }
@@ -755,15 +755,16 @@ __global__ void __launch_bounds__(256) k_adj_stream(const float* __restrict__ mu
 // would read lam_s(t); the adjoint stays in population space between the two,
 // so the storage transform and its inverse drop out, and mu(t) goes to mu_out.
 // The parameter gradients accumulate as in kernel A.
-// Its two gathers and the collision VJP keep the vector units busy two thirds of
-// the time in 2-D (vector components beyond the lattice's dimensions are neither
-// computed nor exchanged: 2048x1024 with three species 228 -> 215 us per reverse
-// step); in 3-D latency bounds it, at few waves.  Asked for three waves per SIMD
-// the D3Q19 build takes 168 VGPRs (192 with three species before) and a compute
-// unit holds more work-groups: 128x96x64 with three species 235 -> 167 us per
-// reverse step, tiles and their order included.  (With three species it spills
-// for that: 10 registers, 44 B of scratch a lane, 7 and 32 B in blocks of 32 x 2.
-// Four take 214 and are left at the two waves that is.)  Each species hands on the
+// Its two gathers and the collision VJP keep the vector units busy half of the
+// time (2048x1024 with three species 0.53 at 2.3 waves per SIMD, 128x96x64 0.47 at
+// 2.2); the rest is latency at these few waves.  In 2-D, vector components beyond
+// the lattice's dimensions are neither computed nor exchanged (2048x1024 with three
+// species 228 -> 215 us per reverse step).  In 3-D, asked for three waves per SIMD,
+// the build takes 158 VGPRs for two species and 168 for three (192 before), and a
+// compute unit holds more work-groups: 128x96x64 with three species 235 -> 167 us
+// per reverse step, tiles and their order included.  With three species it spills
+// for that: 10 registers, 44 B of scratch a lane (7 and 32 B in blocks of 32 x 2).
+// Four take 214 and are left at the two waves that is.  Each species hands on the
 // 3 D + N values that the others' shares follow from, instead of D + 1 +
 // (D + 2) N shares, which saves LDS and arithmetic on the sending side: 216 ->
 // 211 and 166 -> 160 us.

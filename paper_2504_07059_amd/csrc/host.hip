@@ -786,15 +786,18 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, i
     t.bx = 64;
     t.by = 1;
     t.split = 1;
-    // The chip holds one wave per species, 6 waves per SIMD in 2-D and 4 in
-    // 3-D.  us per step at 1, 2, 4, 6, 8, 16, 32 layers: 4096x1024 three
+    // The chip is taken to hold 6 waves per SIMD in 2-D and 4 in 3-D, one per
+    // species of a work-group.  (By their registers the 2-D builds allow 8, 7 and 6
+    // for two, three and four species past the caches and 7, 6 and 5 within them,
+    // the 3-D ones 4; the largest lattices would still gain a few per cent from
+    // taller tiles: 512 tubes 1057 at the height taken, 1004 autotuned.)  us per step at 1, 2, 4, 6, 8, 16, 32 layers: 4096x1024 three
     // species 231, 199, 190, 189, 190, 196, 204 (4 taken); 512x512 binary 9.8,
     // 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary 40, 37.2, 37.9, 42,
     // 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).  Against eight
     // tiles per compute unit, up to 32 layers (16 in 3-D), taken before:
     // 4096x1024 204 -> 189, 512 tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
-    // (Strips: 4 waves per SIMD and a halo of two layers.  1, 2, 4, 6, 10, 16
-    // layers: 4096x1024 three species 407, 311, 269, 253, 253, 265; 1024x64
+    // (Strips: 4 waves per SIMD, of which the quaternary build within the caches
+    // allows 3, and a halo of two layers.  1, 2, 4, 6, 10, 16 layers: 4096x1024 three species 407, 311, 269, 253, 253, 265; 1024x64
     // quaternary 15.3, 13.5, 17.4, 21, 30, 46.)
     const bool strip = strips_pay(p, n_lattices, dim);
     const int64_t cap = (int64_t)cus * (4 * (dim == 3 || strip ? 4 : 6) / ns);
@@ -954,8 +957,9 @@ lbm_mc_status build_adj_tiles(lbm_mc_ctx* c) {
     const int nxb = (q.nx + bx - 1) / bx, nyb = c->DIM == 3 ? (q.ny + by - 1) / by : 1;
     const int64_t cols = (int64_t)nxb * nyb;
     // Work-groups of the fused pass (one wave per species) a compute unit
-    // holds: three waves per SIMD; two with four species and in the build for
-    // 2-D lattices that stay in the caches.  Against eight tiles per
+    // is taken to hold: three waves per SIMD; two with four species and in the
+    // build for 2-D lattices that stay in the caches.  (By their registers the
+    // binary 2-D builds allow one more: 115 past the caches, 158 within.)  Against eight tiles per
     // compute unit in column order, up to 16 layers, taken before, us per
     // reverse step: 2048x1024 three species 259 -> 229, 1024x1024 binary 93 ->
     // 79, 700x300 three species 55 -> 38, 96x96x96 binary 239 -> 212, 96x64x64
@@ -1234,6 +1238,8 @@ static lbm_mc_status init_impl(const lbm_mc_params* p, int32_t n_lattices, const
     if (hipMalloc(&c->dlp, n_lattices * sizeof(LatParams)) != hipSuccess ||
         hipMalloc(&c->dflag, sizeof(unsigned)) != hipSuccess ||
         hipMalloc(&c->dtotals, (size_t)n_lattices * (c->N + 3) * sizeof(double)) != hipSuccess ||
+        // (read by the density pre-pass's steps alone, which another execution
+        // shape may ask for at any time)
         (p[0].forcing == 2 &&
          hipMalloc(&c->dens, (size_t)lo.nodes_total * c->N * sizeof(float)) != hipSuccess))
         return bail(fail(LBM_MC_ERR_HIP, "device allocation failed"));

@@ -740,7 +740,9 @@ __device__ __forceinline__ void march(const SpanBuf (&B)[NS], const GatherConst&
 
 // The rows a layer reads, in the order they are kept: `z` slots for the rows,
 // `h` slots for the rows whose x neighbours are needed.  REV: the reversed
-// gather of the adjoint (no reference stencil, plane 0 at the node itself).
+// gather of the adjoint (no reference stencil, plane 0 at the node itself).  (The
+// halo slots and their codes serve 3-D; 2-D lays its halos out by plane, see
+// PlaneSlots.)
 template <int LAT, bool REV>
 struct Slots {
     using Fr = Frame<LAT>;
@@ -924,7 +926,7 @@ struct WaveRows {
     }
 };
 
-// The same rows, loaded ahead (2-D).
+// The same rows in registers (2-D: of the next layer; 3-D: the layer's own).
 template <int LAT, bool REV>
 struct WaveRaw {
     float v[Slots<LAT, REV>::Z];

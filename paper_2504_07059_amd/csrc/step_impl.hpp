@@ -162,8 +162,11 @@ __global__ void __launch_bounds__(256) k_step(const float* __restrict__ src, flo
 // state instead of NS, and keeps its marching-axis partial sums in LDS
 // (2 per direction with a marching component: 12 floats per lane in 2-D, 20
 // in 3-D; see kSplitLdsMarch), so several times more waves fit on a SIMD: for
-// states beyond the last-level cache seven in 2-D (65 VGPRs), four in 3-D
-// (124; three with the sums in registers).
+// states beyond the last-level cache eight to six in 2-D (61, 65 and 73 VGPRs for
+// two, three and four species), four in 3-D (100).  What bounds it there: in 2-D
+// HBM (4096x1024 three species, 190 us: 4.8 TB/s) with the vector units 0.66 busy,
+// in 3-D the misses a compute unit's L1 keeps in flight (66 of 800 cycles each on
+// 256x128x128 with four species, 665 us).
 //
 // A work-group may hold W such segments of 64 columns side by side
 // (threadIdx.z = segment; bx * by = 64 W): W consecutive 64-column pieces of
@@ -370,7 +373,7 @@ __device__ __forceinline__ float streamed_density(float P0, const float (&F)[Lat
 // beyond either end in its outer lanes, forms each layer's density as it is
 // gathered, and collides a layer once the next one's density is there.  The x
 // differences are taken across lanes, the y differences over the march.  Bound by
-// the vector units (two thirds busy) and by the populations read and written: the
+// the vector units (0.61 busy) and by the populations read and written: the
 // strip costs two columns of 64 and a layer more per tile, the pre-pass a second
 // read of all of them.  The stores are written back from the L2, where strips
 // share the line between them (3001x700 three species 132 us per step, 136
