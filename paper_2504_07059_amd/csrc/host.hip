@@ -789,16 +789,17 @@ Tuning default_tuning(const lbm_mc_params* p, int n_lattices, int dim, int ns, i
     // The chip is taken to hold 6 waves per SIMD in 2-D and 4 in 3-D, one per
     // species of a work-group.  (By their registers the 2-D builds allow 8, 7 and 6
     // for two, three and four species past the caches and 7, 6 and 5 within them,
-    // the 3-D ones 4; the largest lattices would still gain a few per cent from
-    // taller tiles: 512 tubes 1057 at the height taken, 1004 autotuned.)  us per step at 1, 2, 4, 6, 8, 16, 32 layers: 4096x1024 three
+    // the 3-D ones 4.)  us per step at 1, 2, 4, 6, 8, 16, 32 layers: 4096x1024 three
     // species 231, 199, 190, 189, 190, 196, 204 (4 taken); 512x512 binary 9.8,
     // 9.7, 11.5, 14.5, 17.3, 29, 56 (2); 64x64x64 quaternary 40, 37.2, 37.9, 42,
     // 44, 63, 123 (4); 90x50x33 binary 18.3, 15.3, -, ... (2).  Against eight
     // tiles per compute unit, up to 32 layers (16 in 3-D), taken before:
-    // 4096x1024 204 -> 189, 512 tubes 1160 -> 1066, 90x50x33 18.5 -> 15.3.
+    // 4096x1024 204 -> 189, 512 tubes 1061 -> 981 (the gather's wave form
+    // included), 90x50x33 18.5 -> 15.3.
     // (Strips: 4 waves per SIMD, of which the quaternary build within the caches
-    // allows 3, and a halo of two layers.  1, 2, 4, 6, 10, 16 layers: 4096x1024 three species 407, 311, 269, 253, 253, 265; 1024x64
-    // quaternary 15.3, 13.5, 17.4, 21, 30, 46.)
+    // allows 3, and a halo of two layers.  1, 2, 4, 6, 10, 16 layers: 4096x1024
+    // three species 407, 311, 269, 253, 253, 265; 1024x64 quaternary 15.3, 13.5,
+    // 17.4, 21, 30, 46.)
     const bool strip = strips_pay(p, n_lattices, dim);
     const int64_t cap = (int64_t)cus * (4 * (dim == 3 || strip ? 4 : 6) / ns);
     t.rows = cheapest_rows(dim == 3 ? 16 : (strip ? 12 : 6), strip ? 2 : 1, cap, [&](int r) {

@@ -280,7 +280,7 @@ struct SplitOp {
 // Where the species-split step keeps its marching partial sums: in LDS,
 // except for 2-D states held in the last-level cache (written-through
 // stores), where one tile's chain sets the step time and registers are
-// faster (6.23 against 6.31 us per step on the 1024x64 tube).
+// faster (5.73 against 5.90 us per step on the 1024x64 tube).
 template <int LAT, int POL>
 constexpr bool kSplitLdsMarch = Lat<LAT>::DIM == 3 || POL != kStoreWT;
 
